@@ -124,8 +124,8 @@ typedef struct {
   int64_t n_tile_pairs;    /* (tile, primitive) entries of the culling lists           */
   int64_t n_ray_pairs;     /* (ray, primitive) pairs with at least one sample           */
   int64_t device_bytes;    /* device memory held by the structure                       */
-  int32_t pairs_in_forward; /* 1: the first forward builds the per-ray lists, tile by tile;
-                             * 0: the build's pairs kernel did                            */
+  int32_t pairs_in_forward; /* 1: the first forward launches the kernel that builds the
+                             * per-ray lists; 0: the build did                            */
   int32_t reserved;
 } mvp_accel_info;
 
@@ -149,11 +149,11 @@ const char *mvp_version(void);
  * the fixed-step sample interval inside each (the ray-specific lists and
  * domain of integration of Sec. 3.2.1).  cams is a HOST array of n_views.
  * Reads prims->pos/rot/scale; the payload is not read.  BLOCKS until the list
- * sizes are known (one stream synchronisation).  The per-ray lists are built
- * on the device by the first mvp_render_fwd* on the structure (each workgroup
- * builds its screen tile's lists and then marches them), or by the first
- * backward if it comes first; the lists the backward reads per primitive are
- * built on the context's second stream after that first forward.  Calls on one
+ * sizes are known (one stream synchronisation).  The kernel that builds the
+ * per-ray lists is launched by the build or, on large structures (see
+ * mvp_accel_info), by the first mvp_render_fwd* or backward on the structure;
+ * the lists the backward reads per primitive are built on the context's second
+ * stream after that.  Calls on one
  * structure must be ordered on the caller's streams.  *out must be released
  * with mvp_accel_destroy. */
 mvp_status mvp_build_accel(mvp_ctx *ctx, const mvp_prims *prims, const mvp_camera *cams,
@@ -257,9 +257,9 @@ mvp_status mvp_accel_counts(mvp_ctx *ctx, const mvp_accel *accel, uint64_t *ray_
 /* Load counts of the most recent forward and backward on this structure
  * (BLOCKS on `stream`), written to the HOST array out[9]:
  *   [0] ray-samples, [1] prim-samples (as mvp_accel_counts);
- *   forward: [2] voxel-corner sets loaded (8 corners each), [3] pair-record
- *   loads (16 B each), [4] culling-entry frames read from device memory
- *   (52 B each; a tile's frames are staged once per tile when they fit);
+ *   forward: [2] voxel-corner sets loaded (8 corners each, one per prim-sample
+ *   evaluated), [3] pair-record loads (16 B each), [4] culling-entry frames
+ *   read (52 B each, one per record);
  *   backward: [5] pairs visited by its ordering pass, [6] pairs replayed,
  *   [7] cell runs (one voxel-corner set loaded each), [8] non-zero payload
  *   gradient values added to grad_payload.

@@ -392,7 +392,7 @@ mvp_status build_accel(mvp_ctx *ctx, const mvp_prims *prims, const mvp_camera *c
   const size_t sb = scan_scratch_bytes(std::max<size_t>(std::max<size_t>(ntile, (size_t)N), (size_t)kPrimBuckets));
   if (admit) {
     const size_t base = n_views * sizeof(DevCam) + 3 * (size_t)N * 16 + 2 * (ntile + 1) * 8 + R * 16 + 16 +
-                        kNumCounters * 8 + (size_t)n_views * N * 20 + 2 * ntile * 4 + sb + 10 * 256 +
+                        kCntSlots * kCntStride * 8 + (size_t)n_views * N * 20 + 2 * ntile * 4 + sb + 10 * 256 +
                         (rays ? R * 12 + ntile * 12 + 3 * 256 : 0);
     MVP_CHECK(admit->fn(admit->user, base));
   }
@@ -402,7 +402,7 @@ mvp_status build_accel(mvp_ctx *ctx, const mvp_prims *prims, const mvp_camera *c
   MVP_CHECK(keep.get(&a->pair_base, ntile + 1));
   MVP_CHECK(keep.get(&a->ray_seg, R ? R : 1));
   MVP_CHECK(keep.get(&a->ray_nj, R ? R : 1));
-  MVP_CHECK(keep.get(&a->counters, kNumCounters));
+  MVP_CHECK(keep.get(&a->counters, kCntSlots * kCntStride));
   MVP_CHECK(ltmp.get(&rect, (size_t)n_views * N));
   MVP_CHECK(temp.get(&depth, (size_t)n_views * N));
   MVP_CHECK(temp.get(&tile_cnt, ntile));
@@ -427,7 +427,7 @@ mvp_status build_accel(mvp_ctx *ctx, const mvp_prims *prims, const mvp_camera *c
   } else {
     MVP_HIP(hipMemcpyAsync(a->cams, a->cams_host.data(), cam_bytes, hipMemcpyHostToDevice, s));
   }
-  MVP_HIP(launch_zero_u64((uint64_t *)a->counters, kNumCounters, s));
+  MVP_HIP(launch_zero_u64((uint64_t *)a->counters, kCntSlots * kCntStride, s));
   uint32_t *flag = nullptr;
   if (rays) {
     // ray subset: a private copy of the pixel ids, binned into screen tiles
@@ -506,15 +506,12 @@ mvp_status build_accel(mvp_ctx *ctx, const mvp_prims *prims, const mvp_camera *c
   MVP_HIP(launch_segment_sort(a->tile_off, a->tile_list, (int64_t)ntile, depth, N, tx * ty, s));
   a->item_entries = backward_item_entries(prims->M);
   a->n_items_max = for_backward ? (int64_t)(n_tile_pairs / a->item_entries) + N : 0;
-  // Every ray's pairs, the entry frames and the per-entry pair lists: either
-  // by the pairs kernel now, or by the first forward, each workgroup building
-  // its tile's pairs just before marching them.  Fusing pays where the march
-  // has latency to hide the pairs pass in (payloads of at most 8^3, which stay
-  // in the caches) and the grid has enough tiles (32 per CU) for the pairs
-  // phases of some workgroups to overlap the marching of others; elsewhere the
-  // pairs kernel, at its own higher occupancy, is faster.
+  // Every ray's pairs, the entry frames and the per-entry pair lists: by the
+  // pairs kernel now, with the transposed lists beside it, or, where the march
+  // is long enough to hide those (8192 tiles of payloads of at most 8^3), with
+  // the first forward, so that their launches are off the path to it.
   a->po = PairsOut{a->ef, a->pr, a->ray_seg, a->ray_nj, a->ent_base, a->ent_n, a->ent_tile, a->ent_rec,
-                   a->counters + kCntPairs};
+                   a->counters};
   // MVP_PAIRS_IN_FORWARD=1 or 0 overrides the choice (tests and tuning)
   const char *force = getenv("MVP_PAIRS_IN_FORWARD");
   const bool fuse = force && (force[0] == '0' || force[0] == '1') ? force[0] == '1' : prims->M <= 8 && ntile >= 8192;
@@ -531,7 +528,7 @@ mvp_status build_accel(mvp_ctx *ctx, const mvp_prims *prims, const mvp_camera *c
   a->n_ray_pairs = -1;   // read from the device on demand (mvp_accel_get_info)
   a->pair_capacity = capacity;
   a->bytes = (int64_t)(n_views * sizeof(DevCam) + 3 * (size_t)N * 16 + 2 * (ntile + 1) * 8 + R * 16 +
-                       kNumCounters * 8 +
+                       kCntSlots * kCntStride * 8 +
                        (for_backward ? n_tile_pairs * (4 + 4 + 48 + 8 + 16 + 4) + (size_t)N * 24 + capacity * 24
                                      : n_tile_pairs * (4 + 48) + capacity * 16) +
                        (rays ? R * 12 + (ntile + 1) * 8 : 0));
@@ -688,9 +685,9 @@ mvp_status mvp_accel_get_info(const mvp_accel *a, mvp_accel_info *info) {
   if (a->n_ray_pairs < 0 && !a->pairs_pending.load()) {   // counted on the device by the pass that built them
     MVP_HIP(hipSetDevice(a->ctx->device));
     MVP_HIP(hipEventSynchronize(a->pairs_done));
-    uint64_t n = 0;
-    MVP_HIP(hipMemcpy(&n, a->counters + kCntPairs, sizeof n, hipMemcpyDeviceToHost));
-    const_cast<mvp_accel *>(a)->n_ray_pairs = (int64_t)n;
+    uint64_t c[kCntSlots * kCntStride];
+    MVP_HIP(hipMemcpy(c, a->counters, sizeof c, hipMemcpyDeviceToHost));
+    const_cast<mvp_accel *>(a)->n_ray_pairs = (int64_t)sum_counter(c, kCntPairs);
   }
   info->n_views = a->V; info->width = a->W; info->height = a->H; info->n_prim = a->N;
   info->n_tile_pairs = a->n_tile_pairs; info->n_ray_pairs = a->n_ray_pairs; info->device_bytes = a->bytes;
@@ -762,20 +759,26 @@ mvp_status mvp_timing_stop(mvp_ctx *ctx) {
   return MVP_OK;
 }
 
+// The per-ray pairs, if the build left them to the first forward or backward.
+static mvp_status pairs_ready(const mvp_accel *a, hipStream_t s) {
+  if (!a->pairs_pending.exchange(false)) return MVP_OK;
+  hipError_t e = launch_pairs(a->view(2), a->po, s);
+  if (e == hipSuccess) e = hipEventRecord(a->pairs_done, s);
+  if (e != hipSuccess) a->pairs_pending.store(true);
+  MVP_HIP(e);
+  return MVP_OK;
+}
+
 static mvp_status render_fwd(mvp_ctx *ctx, const mvp_accel *a, const mvp_prims *prims, const float *bg,
                              float *rgba, mvp_ray_aux *aux, hipStream_t s) {
   MVP_CHECK(check_render(ctx, a, prims));
   if (!rgba && a->n_slots > 0) { set_error("rgba is NULL"); return MVP_ERR_INVALID; }
   MVP_HIP(hipSetDevice(ctx->device));
-  MVP_HIP(launch_zero_u64((uint64_t *)a->counters, kCntFwdPab + 1, s));
+  MVP_HIP(launch_zero_counters(a->counters, 0, kCntFwdPab + 1, s));
+  MVP_CHECK(pairs_ready(a, s));
   const auto ev = timer_slot(ctx, MVP_KERNEL_FWD_MARCH);
   if (ev.first) MVP_HIP(hipEventRecord(ev.first, s));
-  // the first forward builds the pairs, tile by tile, before marching them
-  const bool build = a->pairs_pending.exchange(false);
-  hipError_t e = launch_march_fwd(a->view(prims->M), *prims, bg, rgba, aux, a->counters, s, build ? &a->po : nullptr);
-  if (e == hipSuccess && build) e = hipEventRecord(a->pairs_done, s);
-  if (e != hipSuccess && build) a->pairs_pending.store(true);
-  MVP_HIP(e);
+  MVP_HIP(launch_march_fwd(a->view(prims->M), *prims, bg, rgba, aux, a->counters, s));
   if (ev.second) MVP_HIP(hipEventRecord(ev.second, s));
   return launch_lists(a);
 }
@@ -783,12 +786,7 @@ static mvp_status render_fwd(mvp_ctx *ctx, const mvp_accel *a, const mvp_prims *
 // What the backward reads of the structure: the pairs (built here if no
 // forward has built them) and the transposed lists (made on the side stream).
 static mvp_status bwd_ready(const mvp_accel *a, hipStream_t s) {
-  if (a->pairs_pending.exchange(false)) {
-    hipError_t e = launch_pairs(a->view(2), a->po, s);
-    if (e == hipSuccess) e = hipEventRecord(a->pairs_done, s);
-    if (e != hipSuccess) a->pairs_pending.store(true);
-    MVP_HIP(e);
-  }
+  MVP_CHECK(pairs_ready(a, s));
   MVP_CHECK(launch_lists(a));
   if (a->lists) MVP_HIP(hipStreamWaitEvent(s, a->lists, 0));
   return MVP_OK;
@@ -865,11 +863,11 @@ mvp_status mvp_accel_counts(mvp_ctx *ctx, const mvp_accel *a, uint64_t *ray_samp
   if (!ctx || !a || a->ctx != ctx || !ray_samples || !prim_samples) { set_error("bad argument"); return MVP_ERR_INVALID; }
   hipStream_t s = (hipStream_t)stream;
   MVP_HIP(hipSetDevice(ctx->device));
-  uint64_t h[2] = {0, 0};
+  uint64_t h[kCntSlots * kCntStride];
   MVP_HIP(hipMemcpyAsync(h, a->counters, sizeof h, hipMemcpyDeviceToHost, s));
   MVP_HIP(hipStreamSynchronize(s));
-  *ray_samples = h[0];
-  *prim_samples = h[1];
+  *ray_samples = sum_counter(h, kCntRaySamples);
+  *prim_samples = sum_counter(h, kCntPrimSamples);
   return MVP_OK;
 }
 
@@ -877,8 +875,10 @@ mvp_status mvp_accel_load_counts(mvp_ctx *ctx, const mvp_accel *a, uint64_t *out
   if (!ctx || !a || a->ctx != ctx || !out) { set_error("bad argument"); return MVP_ERR_INVALID; }
   hipStream_t s = (hipStream_t)stream;
   MVP_HIP(hipSetDevice(ctx->device));
-  MVP_HIP(hipMemcpyAsync(out, a->counters, (kCntBwdFlush + 1) * sizeof(uint64_t), hipMemcpyDeviceToHost, s));
+  uint64_t h[kCntSlots * kCntStride];
+  MVP_HIP(hipMemcpyAsync(h, a->counters, sizeof h, hipMemcpyDeviceToHost, s));
   MVP_HIP(hipStreamSynchronize(s));
+  for (int c = 0; c <= kCntBwdFlush; ++c) out[c] = sum_counter(h, c);
   return MVP_OK;
 }
 

@@ -119,12 +119,11 @@ struct mvp_accel {
   uint2 *ent_rec = nullptr;            // per-entry pair lists
   uint64_t pair_capacity = 0;
   bool for_backward = true;            // false: no per-entry or transposed lists (forward only)
-  bool pairs_in_forward = false;       // the first forward builds the pairs
+  bool pairs_in_forward = false;       // the first forward launches the pairs kernel
   hipEvent_t built = nullptr;          // recorded on the build's stream after its kernels
   hipEvent_t lists = nullptr;          // recorded on the side stream once the transposed lists are built
-  // The per-ray pairs are built by the first forward (each workgroup builds its
-  // tile's pairs, then marches them) or, if a backward comes first, by the
-  // pairs kernel; pairs_done is recorded after whichever did it.
+  // With pairs_in_forward the pairs kernel is launched by the first forward or
+  // backward; pairs_done is recorded after it.
   mvp::PairsOut po{};
   mutable std::atomic<bool> pairs_pending{false};
   mutable hipEvent_t pairs_done = nullptr;

@@ -44,6 +44,14 @@ __global__ void k_zero_u64(uint64_t *p, size_t n) {
   for (; i < n; i += stride) p[i] = 0ull;
 }
 
+__global__ void k_zero_counters(unsigned long long *c, int first, int n) {
+  for (int i = threadIdx.x; i < kCntSlots * n; i += blockDim.x) c[(i / n) * kCntStride + first + i % n] = 0ull;
+}
+hipError_t launch_zero_counters(unsigned long long *counters, int first, int n, hipStream_t s) {
+  hipLaunchKernelGGL(k_zero_counters, dim3(1), dim3(256), 0, s, counters, first, n);
+  return hipGetLastError();
+}
+
 static unsigned grid_for(size_t n, unsigned block) {
   size_t g = (n + block - 1) / block;
   if (g > 65535u * 8u) g = 65535u * 8u;

@@ -106,9 +106,8 @@ struct AccelView {
   const uint32_t *tile_rays;   // or nullptr
 };
 
-// Where a tile's pairs go (see AccelView for the layouts).  Not restrict: the
-// forward march reads them back through its AccelView after a barrier.  The
-// per-entry lists (ent_*) are null for a structure built for the forward only.
+// Where a tile's pairs go (see AccelView for the layouts).  The per-entry lists
+// (ent_*) are null for a structure built for the forward only.
 struct PairsOut {
   float4 *ef;
   int4 *pr;
@@ -118,86 +117,12 @@ struct PairsOut {
   uint32_t *ent_n;
   uint32_t *ent_tile;
   uint2 *ent_rec;
-  unsigned long long *n_pairs;
+  unsigned long long *counters;   // adds to kCntPairs
 };
 
-// Workgroups are dispatched round-robin over the 8 XCDs (each with its own L2):
-// workgroup b runs on XCD b % 8.  Launching kXcd * ceil(n / kXcd) workgroups and
-// mapping b -> (b % kXcd) * per + b / kXcd gives every XCD a contiguous band of
-// tiles, so neighbouring tiles (which share primitives) share an L2.  Returns
-// -1 for the padding workgroups.
+// Workgroups are dispatched round-robin over the 8 XCDs, each with its own L2:
+// workgroup b runs on XCD b mod 8.
 constexpr int kXcd = 8;
-__device__ __forceinline__ int xcd_tile(int b, int n) {
-  const int per = (n + kXcd - 1) / kXcd;
-  const int t = (b % kXcd) * per + b / kXcd;
-  return t < n ? t : -1;
-}
-__host__ __device__ __forceinline__ int xcd_grid(int n) { return kXcd * ((n + kXcd - 1) / kXcd); }
-
-// Position s of the schedule -> tile index (v*T + ty*tiles_x + tx), visiting
-// each view in blocks of kTileBlock x kTileBlock tiles (row-major blocks,
-// row-major inside a block; edge blocks are cut to the grid).  The workgroups
-// resident on one XCD at a time then cover a compact patch of the screen, whose
-// primitives fit its L2 far better than a full-width stripe.
-constexpr int kTileBlock = 8;
-__device__ __forceinline__ int blocked_tile(int s, int tiles_x, int tiles_y) {
-  const int T = tiles_x * tiles_y;
-  const int v = s / T;
-  const int r = s - v * T;
-  const int by = r / (kTileBlock * tiles_x);
-  const int rr = r - by * kTileBlock * tiles_x;
-  const int hb = min(kTileBlock, tiles_y - by * kTileBlock);
-  const int bx = rr / (kTileBlock * hb);
-  const int q = rr - bx * kTileBlock * hb;
-  const int wb = min(kTileBlock, tiles_x - bx * kTileBlock);
-  return v * T + (by * kTileBlock + q / wb) * tiles_x + bx * kTileBlock + q % wb;
-}
-
-// Number of times each view's schedule is halved (first by rows, then by
-// columns, alternately) so that the XCDs sharing a view get one part each:
-// log2(kXcd / V) for V < kXcd views, else 0.
-__host__ __device__ __forceinline__ int view_splits(int V) {
-  int l = 0;
-  while (l < 3 && (V << (l + 1)) <= kXcd) ++l;
-  return l;
-}
-
-// The march's schedule: the view's tiles cut by `levels` halvings into
-// rectangles (top before bottom, left before right), each visited in blocks as
-// blocked_tile does.  With the XCDs' contiguous shares of the schedule
-// (xcd_tile) each XCD then marches one compact rectangle (for two views, a
-// quadrant each) rather than a full-width stripe: its block rows are shorter,
-// so neighbouring block rows, which share primitives, follow each other
-// sooner in the XCD's L2.
-__device__ __forceinline__ int split_tile(int s, int tiles_x, int tiles_y, int levels) {
-  const int T = tiles_x * tiles_y;
-  const int v = s / T;
-  int r = s - v * T;
-  int x0 = 0, y0 = 0, w = tiles_x, h = tiles_y;
-  for (int l = 0; l < levels; ++l) {
-    if (!(l & 1)) {   // rows: top part first
-      const int h0 = (h + 1) / 2;
-      if (r < w * h0) {
-        h = h0;
-      } else {
-        r -= w * h0;
-        y0 += h0;
-        h -= h0;
-      }
-    } else {          // columns: left part first
-      const int w0 = (w + 1) / 2;
-      if (r < w0 * h) {
-        w = w0;
-      } else {
-        r -= w0 * h;
-        x0 += w0;
-        w -= w0;
-      }
-    }
-  }
-  const int lt = blocked_tile(r, w, h);
-  return v * T + (y0 + lt / w) * tiles_x + x0 + lt % w;
-}
 
 // Ray number t (0 <= t < 256, row-major in the 16x16 tile) of `tile`: its
 // slot, view and pixel.  Returns false if there is no such ray (a tile cut by
@@ -284,7 +209,12 @@ __device__ __forceinline__ void slot_pixel(const AccelView &av, size_t slot, int
 }
 
 // Per-structure counters (uint64), written by the most recent forward (the
-// first five) and backward (the last four) on the structure.
+// first five) and backward (the last four) on the structure.  Every wave of the
+// march adds its own counts at its end, and atomics on one address are
+// serialised at the L2 (about 4 ns each: 10 ms for the 524,288 waves of a
+// forward of 4 views of 1024^2, five adds each), so each counter has kCntSlots
+// copies on lines of their own; a workgroup adds to the copy of its index, and
+// a reader sums them.
 enum : int {
   kCntRaySamples = 0,   // samples inside >= 1 primitive, up to the stop
   kCntPrimSamples = 1,  // (sample, primitive) pairs: trilinear fetches
@@ -299,10 +229,21 @@ enum : int {
   kCntSizes = 10,       // build: culling-list entries, pair capacity, ray-subset flags (3 words)
   kNumCounters = 13
 };
+constexpr int kCntSlots = 64, kCntStride = 16;   // counter c of copy s at [s * kCntStride + c]
+__device__ __forceinline__ unsigned long long *counter_slot(unsigned long long *counters) {
+  return counters + (blockIdx.x & (kCntSlots - 1)) * kCntStride;
+}
+inline uint64_t sum_counter(const uint64_t *copies, int c) {   // of a host copy of all slots
+  uint64_t s = 0;
+  for (int i = 0; i < kCntSlots; ++i) s += copies[i * kCntStride + c];
+  return s;
+}
 
 // ---- launchers (return the first HIP error) --------------------------------
 hipError_t launch_zero_u32(uint32_t *p, size_t n, hipStream_t s);
 hipError_t launch_zero_u64(uint64_t *p, size_t n, hipStream_t s);
+// clear counters first .. first + n - 1 in every slot
+hipError_t launch_zero_counters(unsigned long long *counters, int first, int n, hipStream_t s);
 // exclusive scan of n uint32 counts into n+1 uint64 offsets (scratch from scan_scratch_bytes)
 size_t scan_scratch_bytes(size_t n);
 hipError_t launch_scan_u32_u64(const uint32_t *in, uint64_t *out, size_t n, void *scratch, hipStream_t s);
@@ -342,7 +283,7 @@ hipError_t launch_gather_sizes(const uint64_t *n_entries, const uint64_t *capaci
 hipError_t launch_tile_capacity(const uint32_t *tile_cnt, const uint32_t *tile_rays_cnt, size_t ntile, uint32_t *cap,
                                 hipStream_t s);
 // the (ray, primitive) pairs of every ray, the entry frames and the per-entry
-// pair lists (see AccelView); adds the number of pairs to *n_pairs
+// pair lists (see AccelView); counts the pairs (kCntPairs)
 hipError_t launch_pairs(const AccelView &av, const PairsOut &o, hipStream_t s);
 // debug hit sets: per ray the number of slab hits (with or without samples),
 // then their primitive ids in increasing order at ids[off[ray] ..]
@@ -350,11 +291,8 @@ hipError_t launch_hit_count(const AccelView &av, uint32_t *ray_cnt, hipStream_t 
 hipError_t launch_hit_ids(const AccelView &av, const uint64_t *off, int32_t *ids, hipStream_t s);
 
 // bg: optional background [rays,3] composited under the premultiplied colour
-// build_pairs != nullptr: each workgroup first computes its tile's pairs (as
-// launch_pairs does) and then marches them.
 hipError_t launch_march_fwd(const AccelView &av, const mvp_prims &p, const float *bg, float *rgba,
-                            mvp_ray_aux *aux, unsigned long long *counters, hipStream_t s,
-                            const PairsOut *build_pairs = nullptr);
+                            mvp_ray_aux *aux, unsigned long long *counters, hipStream_t s);
 // backward; scratch holds bwd_scratch_bytes(n_slots) bytes (nothing in it needs
 // to start at zero); bg/rgba/g_bg for a composited forward
 hipError_t launch_march_bwd(const AccelView &av, const mvp_prims &p, int64_t n_items_max,

@@ -117,28 +117,6 @@ __device__ __forceinline__ Cell locate(const float4 &A, const float4 &B, float t
 }
 
 
-// Deterministic in-workgroup compaction of the active pixels of a tile.
-// Returns the number of active pixels; s_list receives their local indices
-// in pixel order.
-__device__ __forceinline__ int compact_tile(bool act, int *s_list, int *s_wave) {
-  const int lane = threadIdx.x & (kWave - 1);
-  const int wave = threadIdx.x / kWave;
-  const unsigned long long m = __ballot(act);
-  const int pre = __popcll(m & ((1ull << lane) - 1ull));
-  if (lane == 0) s_wave[wave] = __popcll(m);
-  __syncthreads();
-  int base = 0, total = 0;
-#pragma unroll
-  for (int w = 0; w < kTileThreads / kWave; ++w) {
-    if (w < wave) base += s_wave[w];
-    total += s_wave[w];
-  }
-  if (act) s_list[base + pre] = threadIdx.x;
-  __syncthreads();
-  return total;
-}
-
-
 // ---------------------------------------------------------------------------
 // forward
 // ---------------------------------------------------------------------------
@@ -196,53 +174,16 @@ __device__ __forceinline__ void corner_fade(const float *tab, const Cell &c, flo
   for (int q = 0; q < 8; ++q) wq[q] = wx[q & 1] * wy[(q >> 1) & 1] * wz[q >> 2];
 }
 
-// A ray's unit direction, read where it is kept (registers, or a column of
-// LDS with a stride, which frees three registers in the forward march).
-struct Dir {
-  const float *p;
-  int stride;
-  __device__ __forceinline__ void get(float d[3]) const {
-    d[0] = p[0];
-    d[1] = p[stride];
-    d[2] = p[2 * stride];
-  }
-};
-
-// Where a ray finds the frames of its tile's culling-list entries: staged in
-// LDS (four float4 per entry: the three rows of A with a_i in .w, then the
-// primitive id as int bits in .x) or, for long lists, the entry frames in
-// device memory.  local() rebuilds the pair's local ray y(t) = a + t b with
-// b = A d in the build's canonical arithmetic, so sample positions and the
-// pair's sample interval come from the same values.
-struct Frames {
-  const float4 *lds;   // [4 * list length] or nullptr
-  uint64_t lb;         // first culling-list entry of the tile
-  // S = 1: the frames are in LDS, S = 0: in device memory, S = -1: in LDS iff
-  // lds is set.  A fixed S keeps the LDS reads LDS instructions (a pointer that
-  // may point to either memory is read with flat loads, which also wait for
-  // every outstanding device-memory load).
-  template <int S = -1>
-  __device__ __forceinline__ void local(const AccelView &av, int pos, const Dir &dir, float4 &A, float4 &B) const {
-    float d[3];
-    dir.get(d);
-    float4 f0, f1, f2;
-    int k;
-    if (S == 1 || (S == -1 && lds)) {
-      f0 = lds[4 * pos];
-      f1 = lds[4 * pos + 1];
-      f2 = lds[4 * pos + 2];
-      k = __float_as_int(lds[4 * pos + 3].x);
-    } else {
-      const uint64_t g = lb + (uint64_t)pos;
-      f0 = av.ef[3 * g];
-      f1 = av.ef[3 * g + 1];
-      f2 = av.ef[3 * g + 2];
-      k = (int)av.tile_list[g];
-    }
-    A = make_float4(f0.w, f1.w, f2.w, __int_as_float(k));
-    B = make_float4(row_dot(f0.x, f0.y, f0.z, d), row_dot(f1.x, f1.y, f1.z, d), row_dot(f2.x, f2.y, f2.z, d), 0.f);
-  }
-};
+// The local ray y(t) = a + t b of the pair formed by a ray of direction d with
+// culling-list entry g: b = A d in the build's canonical arithmetic, so sample
+// positions and the pair's sample interval come from the same values.  A.w
+// holds the primitive id (as int bits).
+__device__ __forceinline__ void entry_ray(const AccelView &av, uint64_t g, const float d[3], float4 &A, float4 &B) {
+  const float4 f0 = av.ef[3 * g], f1 = av.ef[3 * g + 1], f2 = av.ef[3 * g + 2];
+  const int k = (int)av.tile_list[g];
+  A = make_float4(f0.w, f1.w, f2.w, __int_as_float(k));
+  B = make_float4(row_dot(f0.x, f0.y, f0.z, d), row_dot(f1.x, f1.y, f1.z, d), row_dot(f2.x, f2.y, f2.z, d), 0.f);
+}
 
 // Tile of a ray slot.
 __device__ __forceinline__ int slot_tile(const AccelView &av, size_t slot) {
@@ -270,35 +211,10 @@ __device__ __forceinline__ float4 sample_pair(const AccelView &av, const void *p
   return trilerp(v, c);
 }
 
-// Accumulated state of one ray, with its counts of samples and of loads
-// (voxel-corner sets, pair records, entry frames read from device memory).
+// Accumulated state of one ray.
 struct RayState {
-  float T = 0.f, I0 = 0.f, I1 = 0.f, I2 = 0.f, t_prev = -1.0f;
-  int j_end = -1;
-  uint32_t n_ray = 0, n_prim = 0, n_cell = 0, n_pj = 0, n_pab = 0;
+  float T, I0, I1, I2, t_prev;
 };
-
-// One clamped additive step with the summed density sig and summed
-// density-weighted colour (c0,c1,c2) of sample j.  Returns true to stop.
-__device__ __forceinline__ bool composite(RayState &st, int j, float sig, float c0, float c1, float c2,
-                                          float dt, float lim) {
-  st.j_end = j;
-  const float Tn = st.T + sig * dt;
-  if (Tn <= 1.0f) {
-    st.T = Tn;
-    st.I0 = fmaf(c0, dt, st.I0);
-    st.I1 = fmaf(c1, dt, st.I1);
-    st.I2 = fmaf(c2, dt, st.I2);
-    return st.T > lim;
-  }
-  const float w = (1.0f - st.T) / sig;
-  st.I0 = fmaf(c0, w, st.I0);
-  st.I1 = fmaf(c1, w, st.I1);
-  st.I2 = fmaf(c2, w, st.I2);
-  st.t_prev = st.T;
-  st.T = 1.0f;
-  return true;
-}
 
 // Among the ray's pairs [0, n) (sorted by first sample) that contain sample
 // j, the one with the smallest primitive id above `after`; n if none.
@@ -319,18 +235,17 @@ __device__ __forceinline__ int next_by_id(const AccelView &av, uint32_t seg, int
 // Sequential combine at sample j, whose summed step saturates: the
 // primitives containing j in increasing id, each with its own clamp step.
 // Returns true to stop.
-template <bool BF16, bool FADE, bool STAGED>
-__device__ bool seq_sample(const AccelView &av, const Frames &fr, const void *pay, const float *fade, uint32_t seg,
-                           int stride, int n, const Dir &d, int j, RayState &st) {
+template <bool BF16, bool FADE>
+__device__ bool seq_sample(const AccelView &av, uint64_t lb, const void *pay, const float *fade, uint32_t seg,
+                           int stride, int n, const float d[3], int j, RayState &st) {
   const float dt = av.step;
   const float tau = (float)j * dt;
   const float T0 = st.T;
-  st.j_end = j;
   int last = -1;
   for (int i = next_by_id(av, seg, stride, n, j, last); i < n; i = next_by_id(av, seg, stride, n, j, last)) {
     const int4 r = av.pr[seg + i * stride];
     float4 A, B;
-    fr.template local<STAGED ? 1 : 0>(av, r.z, d, A, B);
+    entry_ray(av, lb + (uint64_t)r.z, d, A, B);
     const float4 s = sample_pair<BF16, FADE>(av, pay, fade, A, B, tau);
     const float Tn = st.T + s.w * dt;
     if (Tn <= 1.0f) {
@@ -353,230 +268,444 @@ __device__ bool seq_sample(const AccelView &av, const Frames &fr, const void *pa
   return st.T > 1.0f - av.eps;
 }
 
-// The samples J..J+kWin-1 of a ray are gathered pair by pair into per-sample
-// sums held in registers (a pair's 8 voxel corners stay in registers while
-// consecutive samples remain in one cell), then composited in sample order.
-// The ray's pairs are sorted by (first sample, primitive id): a window visits
-// only the pairs that overlap it, and the primitives of one sample are summed
-// in primitive-id order within each group of pairs with the same first sample.
-constexpr int kWin = 12;
+// The forward gives each ray kWin lanes of a wave, one lane per sample of a
+// window of kWin consecutive samples: a wave marches 64 / kWin = 8 rays (4 x 2
+// pixels).  Every lane evaluates its own sample for each pair of the ray that
+// overlaps the window, pair by pair in the list's order, so that a sample's
+// sums take the primitives in one fixed order; then the window is composited
+// across the ray's lanes.  The pairs of a ray are sorted by (first sample,
+// primitive id): a window visits only a run of the list.
+//
+// Why lanes are samples: with one ray per lane the lanes of a wave change
+// voxel cells at different samples, so the corner loads were issued for 8 of
+// 64 lanes on average, and a gather costs the L1 at least 16 cycles however
+// few lanes it serves (46% of the lanes did work per VALU instruction; 70% do
+// now); and a picture gave the chip one wave per 64 rays, each a long serial
+// chain (256 waves of 4 for 256 x 256 pixels).  The march is now bound by the
+// L1's data return (one 128-byte line per four neighbouring lanes and cycle:
+// about 20 cycles per corner load) with FP32 payloads and by the VALU with
+// BF16 ones.  8 samples rather than 16: a window of 16 leaves 6% more lanes
+// idle at the ends of the pairs and takes more pairs per window.
+// Measured (march and pairs kernels together, one ray per lane -> this):
+// 512 x 16^3 BF16 at 256^2 1.40 -> 0.31 ms, 4096 x 8^3 FP32 at 1024^2
+// 4.15 -> 2.20 ms and four such views 8.0 -> 8.1 ms, 2048 x 12^3 BF16 at
+// 1920 x 1080 5.8 -> 4.2 ms, 32768 x 16^3 BF16 at 2 x 2048^2 21.0 -> 14.1 ms,
+// 16384 sampled rays of four 1024^2 views 2.6 -> 0.45 ms.
+constexpr int kWin = 8;
+constexpr int kRaysPerWave = kWave / kWin;
+// Pairs staged per ray in LDS: a ring, refilled kBatch at a time (each lane
+// takes kBatch / kWin of them), whose slot after the last pair holds a
+// sentinel.  A refill waits for device memory twice (the records, then the
+// frames they name): 16 pairs at a time beat 8 by 4 to 15%.
+constexpr int kRing = 32, kBatch = 16;
 
-// OPAQUE_J (used where the kernel also runs the pairs pass or applies the fade
-// window, and is short of registers): the window start is hidden from
-// loop-invariant code motion, so
-// the window's sample times are recomputed for each pair instead of being held
-// in about two dozen registers across the pair loop.  Same arithmetic either way.
-template <bool BF16, bool FADE, bool OPAQUE_J, bool STAGED>
-__device__ void march_ray(const AccelView &av, const Frames &fr, const void *pay, const float *fade, uint32_t seg,
-                          int stride, int n, const Dir &d, RayState &st) {
-  const float dt = av.step, lim = 1.0f - av.eps;
-  const int M = av.M;
-  const float hM = 0.5f * (float)(M - 1);
-  const size_t M3 = (size_t)M * M * M;
-  int e0 = 0;                  // pairs before e0 have ended before the window
-  int4 q0 = av.pr[seg];        // record e0, kept across windows: it opens the next window's pair loop
-  ++st.n_pj;
-  int J = q0.x;
-  while (true) {
-    float as[kWin], ar[kWin], ag[kWin], ab[kWin];
-    // samples of the window inside at least one primitive, and the number of
-    // primitives containing each, 8 bits per sample (exact when the ray has
-    // at most 255 pairs; longer lists count their prim-samples afterwards)
-    uint32_t occ = 0, cp[kWin / 4] = {};
+// Orders this wave's LDS accesses for its other lanes.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+__device__ __forceinline__ uint64_t ballot(bool b) { return __builtin_amdgcn_ballot_w64(b); }
+
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ int dpp(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true); }
+constexpr int kShr1 = 0x111, kXor1 = 0xb1, kXor2 = 0x4e, kMirror8 = 0x141;
+
+// maximum and minimum over the 8 lanes of a ray, in every one of them
+__device__ __forceinline__ int max8(int v) {
+  v = max(v, dpp<kXor1>(v));
+  v = max(v, dpp<kXor2>(v));
+  return max(v, dpp<kMirror8>(v));
+}
+__device__ __forceinline__ int min8(int v) {
+  v = min(v, dpp<kXor1>(v));
+  v = min(v, dpp<kXor2>(v));
+  return min(v, dpp<kMirror8>(v));
+}
+
+// The ordinary steps of a window, sample by sample in order: T += x,
+// I = fma(c, dt, I), taken by all 8 lanes of a ray alike (the roundings are
+// those of a serial loop).  Step k reads lane k of the ray: lane k or k + 8 of
+// the row of 16 that two rays share, each with the other ray's banks masked.
+// Inline because the compiler does not fold a bank-masked move into the
+// arithmetic; the leading wait covers a write of an operand just before.
+#define MVP_STEP(K, H)                                                                \
+  "v_add_f32_dpp %0, %4, %0 row_newbcast:" #K " row_mask:0xf bank_mask:0x3\n\t"       \
+  "v_fmac_f32_dpp %1, %5, %8 row_newbcast:" #K " row_mask:0xf bank_mask:0x3\n\t"      \
+  "v_fmac_f32_dpp %2, %6, %8 row_newbcast:" #K " row_mask:0xf bank_mask:0x3\n\t"      \
+  "v_fmac_f32_dpp %3, %7, %8 row_newbcast:" #K " row_mask:0xf bank_mask:0x3\n\t"      \
+  "v_add_f32_dpp %0, %4, %0 row_newbcast:" #H " row_mask:0xf bank_mask:0xc\n\t"       \
+  "v_fmac_f32_dpp %1, %5, %8 row_newbcast:" #H " row_mask:0xf bank_mask:0xc\n\t"      \
+  "v_fmac_f32_dpp %2, %6, %8 row_newbcast:" #H " row_mask:0xf bank_mask:0xc\n\t"      \
+  "v_fmac_f32_dpp %3, %7, %8 row_newbcast:" #H " row_mask:0xf bank_mask:0xc\n\t"
+__device__ __forceinline__ void window_steps(float &T, float &I0, float &I1, float &I2, float x, float c0, float c1,
+                                             float c2, float dt) {
+  asm("s_nop 1\n\t" MVP_STEP(0, 8) MVP_STEP(1, 9) MVP_STEP(2, 10) MVP_STEP(3, 11) MVP_STEP(4, 12) MVP_STEP(5, 13)
+          MVP_STEP(6, 14) MVP_STEP(7, 15)
+      : "+v"(T), "+v"(I0), "+v"(I1), "+v"(I2)
+      : "v"(x), "v"(c0), "v"(c1), "v"(c2), "v"(dt));
+}
+#undef MVP_STEP
+
+// The 8 voxel corners of a cell whose corner (0,0,0) is at byte address p.
+template <bool BF16>
+__device__ __forceinline__ void corners_at(const char *p, size_t row, size_t slice, float4 (&v)[8]) {
 #pragma unroll
-    for (int w = 0; w < kWin; ++w) as[w] = ar[w] = ag[w] = ab[w] = 0.f;
-    const int J1 = J + kWin;
-    int4 rn = q0;                // record i; record i + 1 is requested before pair i is marched
-    for (int i = e0; i < n; ++i) {
-      const int4 r = rn;
-      if (r.x >= J1) break;
-      if (i + 1 < n) {   // the next record is in flight while this pair is marched
-        rn = av.pr[seg + (i + 1) * stride];
-        ++st.n_pj;
-      }
-      if (r.y < J) continue;
-      const int lo = max(r.x, J) - J, hi = min(r.y, J1 - 1) - J;
-      occ |= ((2u << hi) - 1u) & ~((1u << lo) - 1u);
-      float4 A, B;
-      fr.template local<STAGED ? 1 : 0>(av, r.z, d, A, B);
-      if (!STAGED) ++st.n_pab;
-      const size_t kb = (size_t)prim_of(A) * M3;
-      int cur = -1;
-      int Jp = J;
-      if (OPAQUE_J) asm volatile("" : "+v"(Jp));
-      float4 v[8];
-#pragma unroll
-      for (int w = 0; w < kWin; ++w) {
-        if (w >= lo && w <= hi) {
-          const float tau = (float)(Jp + w) * dt;
-          const Cell c = locate(A, B, tau, M, hM);
-          if (c.idx != cur) {
-            load_corners<BF16>(pay, kb + c.idx, M, v);
-            ++st.n_cell;
-            if (FADE) {
-              float wq[8];
-              corner_fade(fade, c, wq);
-#pragma unroll
-              for (int q = 0; q < 8; ++q) v[q].w *= wq[q];
-            }
-            cur = c.idx;
-          }
-          const float4 sv = trilerp(v, c);
-          as[w] += sv.w;
-          ar[w] = fmaf(sv.w, sv.x, ar[w]);
-          ag[w] = fmaf(sv.w, sv.y, ag[w]);
-          ab[w] = fmaf(sv.w, sv.z, ab[w]);
-          cp[w / 4] += 1u << (8 * (w % 4));
-        }
-      }
+  for (int r = 0; r < 4; ++r) {
+    const char *q = p + ((r & 1) ? row : 0) + ((r & 2) ? slice : 0);
+    if (BF16) {   // both voxels of an x edge in one load (8-byte aligned)
+      typedef uint32_t u4 __attribute__((ext_vector_type(4), aligned(8)));
+      const u4 w = *(const u4 *)q;
+      v[2 * r] = make_float4(__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xffff0000u),
+                             __uint_as_float(w.y << 16), __uint_as_float(w.y & 0xffff0000u));
+      v[2 * r + 1] = make_float4(__uint_as_float(w.z << 16), __uint_as_float(w.z & 0xffff0000u),
+                                 __uint_as_float(w.w << 16), __uint_as_float(w.w & 0xffff0000u));
+    } else {
+      v[2 * r] = *(const float4 *)q;
+      v[2 * r + 1] = *(const float4 *)(q + 16);
     }
-    // composite the occupied samples in order; a sample whose summed step
-    // saturates under the sequential combine leaves the unrolled loop and is
-    // taken primitive by primitive, then the loop resumes after it
-    bool stop = false;
-    int w0 = 0;
-    while (!stop && w0 < kWin) {
-      int wseq = kWin;
-#pragma unroll
-      for (int w = 0; w < kWin; ++w) {
-        if (w >= w0 && !stop && wseq == kWin && ((occ >> w) & 1u)) {
-          ++st.n_ray;
-          st.n_prim += (cp[w / 4] >> (8 * (w % 4))) & 0xffu;
-          if (av.combine && st.T + as[w] * dt > 1.0f) wseq = w;
-          else stop = composite(st, J + w, as[w], ar[w], ag[w], ab[w], dt, lim);
-        }
-      }
-      if (wseq < kWin) stop = seq_sample<BF16, FADE, STAGED>(av, fr, pay, fade, seg, stride, n, d, J + wseq, st);
-      w0 = wseq + 1;
-    }
-    if (stop) break;
-    // next occupied sample: every pair in front of e0 ends before J1, and all
-    // later pairs start no earlier than e0 does
-    while (q0.y < J1) {
-      if (++e0 == n) break;
-      q0 = av.pr[seg + e0 * stride];
-      ++st.n_pj;
-    }
-    if (e0 == n) break;
-    J = max(J1, q0.x);
-  }
-  if (n > 255) {   // the 8-bit per-sample counts may have wrapped: count the samples up to the last one
-    uint32_t np = 0;
-    for (int i = 0; i < n; ++i) {
-      const int4 r = av.pr[seg + i * stride];
-      np += (uint32_t)max(0, min(r.y, st.j_end) - r.x + 1);
-    }
-    st.n_prim = np;
   }
 }
 
-// Frames of a tile's culling list staged in LDS when the list has at most
-// this many entries.
-constexpr int kFrameLds = 256;
+// The march's schedule over full frames.  Unit u of the launch (one workgroup
+// of one wave: larger workgroups hold their slots until their slowest wave
+// ends, 4 to 10% slower) runs on XCD u mod 8.  The tiles of a view are cut into
+// blocks of kMarchBlock x kMarchBlock (edge blocks padded); blocks are dealt
+// to the XCDs in turn, with an offset that moves from turn to turn, so that
+// every XCD gets blocks from all over the view (the rays that meet primitives
+// usually fill its middle), and an XCD takes the units of one block after
+// another, so that its L2 serves a compact patch of the screen at a time.
+// Blocks of 2 x 2 tiles against 4 x 4: a 256 x 256 picture 0.21 against 0.36 ms
+// (4 x 4 gives each XCD two blocks), 32768 x 16^3 12.6 against 14.5 ms, one
+// 1024^2 view of 4096 x 8^3 1.90 against 1.80 ms.
+constexpr int kMarchBlock = 2;
+constexpr int kUnitW = 4, kUnitH = 2;   // pixels of a unit
+constexpr int kUnitsPerTile = kTileThreads / kRaysPerWave;
+constexpr int kUnitsPerBlock = kMarchBlock * kMarchBlock * kUnitsPerTile;
 
-// BUILD: the workgroup first builds its tile's pairs (the pairs pass of the
-// build, tile_pairs), then marches them; the records it reads back were
-// written by other threads of the workgroup before the barrier.
-template <bool BF16, bool FADE, bool BUILD>
-__global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(3))) void k_march_fwd(
-    AccelView av, const void *__restrict__ pay, const float *__restrict__ bg, float4 *__restrict__ rgba,
-    mvp_ray_aux *__restrict__ aux, unsigned long long *__restrict__ counters, PairsOut po) {
-  __shared__ int s_list[kTileThreads];
-  __shared__ int s_wave[kTileThreads / kWave];
-  __shared__ float4 s_frm[4 * kFrameLds];
-  __shared__ float s_dir[3][kTileThreads];
+__host__ __device__ __forceinline__ int64_t march_units(const AccelView &av) {
+  const int64_t bx = (av.tiles_x + kMarchBlock - 1) / kMarchBlock, by = (av.tiles_y + kMarchBlock - 1) / kMarchBlock;
+  const int64_t blocks = bx * by * av.V;
+  return (blocks + kXcd - 1) / kXcd * kXcd * kUnitsPerBlock;
+}
+
+// Tile and unit within the tile of unit u; false for a padding unit.
+__device__ __forceinline__ bool march_tile(const AccelView &av, int64_t u, int *tile, int *sub) {
+  const int bx = (av.tiles_x + kMarchBlock - 1) / kMarchBlock, by = (av.tiles_y + kMarchBlock - 1) / kMarchBlock;
+  const int x = (int)(u % kXcd);
+  const int m = (int)(u / kXcd / kUnitsPerBlock), r = (int)(u / kXcd % kUnitsPerBlock);
+  const int blk = m * kXcd + ((x + 3 * m) & (kXcd - 1));
+  const int v = blk / (bx * by), b = blk - v * bx * by;
+  const int t = r / kUnitsPerTile;
+  const int ty = (b / bx) * kMarchBlock + t / kMarchBlock, tx = (b % bx) * kMarchBlock + t % kMarchBlock;
+  *sub = r % kUnitsPerTile;
+  *tile = (v * av.tiles_y + ty) * av.tiles_x + tx;
+  return v < av.V && ty < av.tiles_y && tx < av.tiles_x;
+}
+
+// 4 waves per SIMD: 5 spill and crowd the L1 (32768 x 16^3: 23 against 16 ms).
+template <bool BF16, bool FADE, bool SEQ>
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void k_march_fwd(
+    AccelView av, const char *__restrict__ pay, const float *__restrict__ bg, float4 *__restrict__ rgba,
+    mvp_ray_aux *__restrict__ aux, unsigned long long *__restrict__ counters, int64_t n_units) {
+  __shared__ float4 pa[kRing][kRaysPerWave];     // a, first sample (int bits)
+  __shared__ float4 pb[kRing][kRaysPerWave];     // b, last sample (int bits)
+  __shared__ uint64_t pp[kRing][kRaysPerWave];   // address of the primitive's payload
   extern __shared__ float s_fade[];   // [M] when FADE
-  const int slot = xcd_tile(blockIdx.x, av.V * av.tiles_x * av.tiles_y);
-  if (slot < 0) return;
-  const int tile = split_tile(slot, av.tiles_x, av.tiles_y, view_splits(av.V));
-  if (BUILD) {
-    tile_pairs(av, tile, po);
-    __syncthreads();
+  if (FADE) {
+    fill_fade(s_fade, av.M, av.fade_alpha, av.fade_beta);
+    wave_sync();
   }
-  if (FADE) fill_fade(s_fade, av.M, av.fade_alpha, av.fade_beta);   // visible after compact_tile's barrier
-  const uint64_t lb = av.tile_off[tile], len = av.tile_off[tile + 1] - lb;
-  const bool staged = len <= (uint64_t)kFrameLds;
-  unsigned long long n_stage = 0;
-  if (staged) {   // the tile's entry frames (visible after compact_tile's barrier)
-    for (int e = threadIdx.x; e < (int)len; e += kTileThreads) {
-#pragma unroll
-      for (int r = 0; r < 3; ++r) s_frm[4 * e + r] = av.ef[3 * (lb + e) + r];
-      s_frm[4 * e + 3] = make_float4(__int_as_float((int)av.tile_list[lb + e]), 0.f, 0.f, 0.f);
-      ++n_stage;
-    }
-  }
-  int total;
-  {
-    size_t ray;
-    int v, px, py;
-    const bool valid = tile_ray(av, tile, threadIdx.x, &ray, &v, &px, &py);
-    bool act = false;
-    if (valid) {
-      act = av.ray_nj[ray].x > 0;
-      if (!act) {
-        float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (bg) o = make_float4(bg[3 * ray], bg[3 * ray + 1], bg[3 * ray + 2], 0.f);
-        rgba[ray] = o;
-        if (aux) aux[ray] = mvp_ray_aux{-1, -1.0f};
+  const int lane = threadIdx.x;
+  const int w = lane & (kWin - 1), rl = lane / kWin;   // sample of the window, ray of the wave
+  const int M = av.M;
+  const float hM = 0.5f * (float)(M - 1), top = (float)(M - 2), Mf = (float)M;
+  constexpr int kVox = BF16 ? 8 : 16;
+  const uint32_t row = (uint32_t)M * kVox, slice = row * (uint32_t)M;   // bytes
+  const uint64_t prim_bytes = (uint64_t)slice * (uint64_t)M;
+  const float dt = av.step, lim = 1.0f - av.eps;
+  uint32_t n_ray = 0, n_prim = 0, n_cell = 0, n_pj = 0;
+
+  for (int64_t u = blockIdx.x; u < n_units; u += gridDim.x) {
+    // the ray of this lane's group of kWin lanes
+    size_t ray = 0;
+    int tile = 0, v = 0, px = 0, py = 0;
+    bool valid;
+    if (av.tile_rays) {   // ray subset: consecutive entries of the tiles' ray lists
+      const int64_t p = u * kRaysPerWave + rl;
+      valid = p < av.n_slots;
+      if (valid) {
+        ray = av.tile_rays[p];
+        slot_pixel(av, ray, &v, &px, &py);
+        tile = (v * av.tiles_y + py / kTile) * av.tiles_x + px / kTile;
       }
+    } else {
+      int sub;
+      if (!march_tile(av, u, &tile, &sub)) continue;
+      constexpr int kAcross = kTile / kUnitW;
+      const int x = (sub % kAcross) * kUnitW + (rl & 3), y = (sub / kAcross) * kUnitH + (rl >> 2);
+      valid = tile_ray(av, tile, y * kTile + x, &ray, &v, &px, &py);
     }
-    total = compact_tile(act, s_list, s_wave);
-  }
-  RayState st;
-  if ((int)threadIdx.x < total) {
-    size_t ray;
-    int v, px, py;
-    tile_ray(av, tile, s_list[threadIdx.x], &ray, &v, &px, &py);
-    float d[3];
-    pixel_ray(av.cams[v], px, py, d);
-#pragma unroll
-    for (int i = 0; i < 3; ++i) s_dir[i][threadIdx.x] = d[i];
-    const uint32_t seg = (uint32_t)av.ray_seg[ray];
-    const int stride = tile_ray_count(av, tile), n = av.ray_nj[ray].x;
-    const Dir dir{&s_dir[0][threadIdx.x], kTileThreads};
-    if (staged) march_ray<BF16, FADE, BUILD || FADE, true>(av, Frames{s_frm, lb}, pay, s_fade, seg, stride, n, dir, st);
-    else march_ray<BF16, FADE, BUILD || FADE, false>(av, Frames{nullptr, lb}, pay, s_fade, seg, stride, n, dir, st);
-    if (bg) {   // composite over the background: I + (1 - A) B
-      const float u = 1.0f - st.T;
-      st.I0 = fmaf(u, bg[3 * ray], st.I0);
-      st.I1 = fmaf(u, bg[3 * ray + 1], st.I1);
-      st.I2 = fmaf(u, bg[3 * ray + 2], st.I2);
+    int n = 0, stride = 0;
+    uint32_t seg = 0;
+    float d[3] = {0.f, 0.f, 1.f};
+    if (valid) {
+      n = av.ray_nj[ray].x;
+      seg = (uint32_t)av.ray_seg[ray];
+      stride = tile_ray_count(av, tile);
+      pixel_ray(av.cams[v], px, py, d);
     }
-    rgba[ray] = make_float4(st.I0, st.I1, st.I2, st.T);
-    if (aux) aux[ray] = mvp_ray_aux{st.j_end, st.t_prev};
-  }
-  if (counters) {
-    const unsigned long long c[5] = {wave_sum_u64(st.n_ray), wave_sum_u64(st.n_prim), wave_sum_u64(st.n_cell),
-                                     wave_sum_u64(st.n_pj), wave_sum_u64(st.n_pab + n_stage)};
-    if ((threadIdx.x & (kWave - 1)) == 0 && (c[3] | c[4])) {
+    const uint64_t lb = av.tile_off[tile];
+    float T = 0.f, t_prev = -1.0f;
+    float I0 = 0.f, I1 = 0.f, I2 = 0.f;
+    int j_last = -1;                      // the last sample this lane took
+    bool act = n > 0;
+    int e0 = 0;                // pairs before e0 have ended before the window
+    int base = 0, ready = 0;   // pairs [base, ready) are staged; slot `ready` of the ring is the sentinel
+    // stage pairs [ready, ready + kWin) of the ray: one per lane
+    auto stage = [&]() {
+      constexpr int kB = kBatch / kWin;
+      const int i0 = ready + w;
+      int4 r[kB];
 #pragma unroll
-      for (int i = 0; i < 5; ++i) atomicAdd(&counters[i], c[i]);
+      for (int b = 0; b < kB; ++b) r[b] = av.pr[seg + (uint32_t)min(i0 + b * kWin, n - 1) * (uint32_t)stride];
+      ready = min(n, ready + kBatch);
+      base = max(base, ready + 1 - kRing);
+#pragma unroll
+      for (int b = 0; b < kB; ++b) {
+        const int i = i0 + b * kWin, at = i & (kRing - 1);
+        float4 A, B;
+        entry_ray(av, lb + (uint64_t)r[b].z, d, A, B);
+        if (i < n) {
+          pp[at][rl] = (uint64_t)(uint32_t)r[b].w * prim_bytes + (uint64_t)pay;
+          pa[at][rl] = make_float4(A.x, A.y, A.z, __int_as_float(r[b].x));
+          pb[at][rl] = make_float4(B.x, B.y, B.z, __int_as_float(r[b].y));
+          ++n_pj;
+        }
+      }
+      if (w == 0) {   // no pair: starts after every window, ends after every window
+        pa[ready & (kRing - 1)][rl].w = __int_as_float(INT_MAX);
+        pb[ready & (kRing - 1)][rl].w = __int_as_float(INT_MAX);
+      }
+    };
+    wave_sync();   // the ring's last readers (the previous rays) are done
+    if (act) stage();
+    wave_sync();
+    int J = act ? __float_as_int(pa[0][rl].w) : 0;
+    while (ballot(act)) {
+      // keep the pairs of a window staged ahead: once a ray runs short, every
+      // ray of the wave with room is refilled
+      if (ballot(act && ready < n && ready - e0 < kWin)) {
+        if (act && ready < n && ready - e0 <= kRing - 1 - kBatch) stage();
+        wave_sync();
+      }
+      const int j = J + w, J1 = J + kWin;
+      const int j_end = act ? J1 : INT_MIN;
+      const float tau = (float)j * dt;
+      float as = 0.f, ar = 0.f, ag = 0.f, ab = 0.f;   // the sample's sums over its primitives
+      uint32_t cnt = 0;                               // the number of those
+      int i = e0;
+      while (true) {
+        while (true) {
+          const int at = i & (kRing - 1);
+          const float4 A = pa[at][rl];
+          const int jlo = __float_as_int(A.w);
+          const bool more = jlo < j_end;
+          if (!ballot(more)) break;
+          const float4 B = pb[at][rl];
+          i += more ? 1 : 0;
+          if (more && j >= jlo && j <= __float_as_int(B.w)) {
+            const float y0 = fmaf(tau, B.x, A.x), y1 = fmaf(tau, B.y, A.y), y2 = fmaf(tau, B.z, A.z);
+            const float u0 = fmaf(__builtin_amdgcn_fmed3f(y0, -1.0f, 1.0f), hM, hM),
+                        u1 = fmaf(__builtin_amdgcn_fmed3f(y1, -1.0f, 1.0f), hM, hM),
+                        u2 = fmaf(__builtin_amdgcn_fmed3f(y2, -1.0f, 1.0f), hM, hM);
+            const float q0 = __builtin_amdgcn_fmed3f(floorf(u0), 0.0f, top),
+                        q1 = __builtin_amdgcn_fmed3f(floorf(u1), 0.0f, top),
+                        q2 = __builtin_amdgcn_fmed3f(floorf(u2), 0.0f, top);
+            Cell c;
+            c.f[0] = u0 - q0;
+            c.f[1] = u1 - q1;
+            c.f[2] = u2 - q2;
+            c.idx = (int)fmaf(fmaf(q2, Mf, q1), Mf, q0);
+            float4 vx[8];
+            corners_at<BF16>((const char *)(pp[at][rl] + (uint64_t)(uint32_t)c.idx * kVox), row, slice, vx);
+            if (FADE) {
+              c.i[0] = (int)q0;
+              c.i[1] = (int)q1;
+              c.i[2] = (int)q2;
+              float wq[8];
+              corner_fade(s_fade, c, wq);
+#pragma unroll
+              for (int q = 0; q < 8; ++q) vx[q].w *= wq[q];
+            }
+            const float4 sv = trilerp(vx, c);
+            as += sv.w;
+            ar = fmaf(sv.w, sv.x, ar);
+            ag = fmaf(sv.w, sv.y, ag);
+            ab = fmaf(sv.w, sv.z, ab);
+            ++cnt;
+          }
+        }
+        // a ray that ran out of staged pairs within the window
+        const bool dry = act && i == ready && ready < n;
+        if (!ballot(dry)) break;
+        if (dry) stage();
+        wave_sync();
+      }
+      n_cell += cnt;
+      // Composite the window's samples in order (a sample outside every
+      // primitive adds 0).  Opacities are not negative, so a ray stops in this
+      // window iff its last sum exceeds the limit.
+      const float x = as * dt;
+      float Tw = T, J0 = I0, J1c = I1, J2 = I2;
+      window_steps(Tw, J0, J1c, J2, x, ar, ag, ab, dt);
+      const bool mine = cnt > 0;
+      if (!ballot(act && !(Tw <= lim))) {   // no ray of the wave stops here
+        T = Tw;
+        I0 = J0;
+        I1 = J1c;
+        I2 = J2;
+        n_ray += mine ? 1 : 0;
+        n_prim += cnt;
+        j_last = mine ? j : j_last;
+      } else {
+        // A ray's stopping sample is the first whose sum exceeds the limit.  A
+        // sample whose summed step saturates under the sequential combine is
+        // taken primitive by primitive, and the rest of the window after it.
+        int from = 0;   // samples before it are done
+        while (true) {
+          // the opacity after each sample, on its lane: each step adds the
+          // previous lane's sum
+          const float xs = w >= from ? x : 0.f;
+          const float t0 = T + xs;
+          float t = t0;
+#pragma unroll
+          for (int s = 1; s < kWin; ++s) {
+            const float up = dpp<kShr1>(t) + xs;
+            t = w == 0 ? t0 : up;
+          }
+          const int ws = min8(act && w >= from && !(t <= lim) ? w : kWin);
+          const int src = (lane & ~(kWin - 1)) | min(ws, kWin - 1);
+          const float tw = __shfl(t, src, kWave);          // after the stopping (or the last) sample
+          const bool over = ws < kWin && !(tw <= 1.0f);   // it is not an ordinary step
+          if (act && mine && w >= from && w <= ws) {
+            ++n_ray;
+            n_prim += cnt;
+            j_last = j;
+          }
+          // the ordinary steps
+          const bool ord = act && w >= from && (w < ws || (w == ws && !over));
+          float Tn = T;
+          window_steps(Tn, I0, I1, I2, ord ? x : 0.f, ord ? ar : 0.f, ord ? ag : 0.f, ord ? ab : 0.f, dt);
+          const float s0 = __shfl(ar, src, kWave), s1 = __shfl(ag, src, kWave), s2 = __shfl(ab, src, kWave),
+                      ss = __shfl(as, src, kWave);
+          bool again = false;
+          if (act) {
+            T = Tn;
+            if (!over) {
+              act = ws == kWin;
+            } else if (!SEQ) {
+              const float wgt = (1.0f - T) / ss;
+              I0 = fmaf(s0, wgt, I0);
+              I1 = fmaf(s1, wgt, I1);
+              I2 = fmaf(s2, wgt, I2);
+              t_prev = T;
+              T = 1.0f;
+              act = false;
+            } else {   // every lane of the ray takes the same walk
+              RayState st{T, I0, I1, I2, -1.0f};
+              const bool stop = seq_sample<BF16, FADE>(av, lb, pay, s_fade, seg, stride, n, d, J + ws, st);
+              T = st.T;
+              I0 = st.I0;
+              I1 = st.I1;
+              I2 = st.I2;
+              if (stop) {
+                t_prev = st.t_prev;
+                act = false;
+              } else {
+                again = ws + 1 < kWin;
+              }
+            }
+          }
+          from = again ? ws + 1 : kWin;   // kWin: done with this window
+          if (!SEQ || !ballot(again)) break;
+        }
+      }
+      // next window: the first pair that reaches past this one, or the first
+      // sample of the next pair (all pairs after e0 start no earlier than e0 does)
+      while (true) {
+        if (ballot(act && e0 < base)) {   // pushed out by a window over more pairs than the ring holds
+          if (act && e0 < base) {
+            ready = e0;
+            base = e0;
+            stage();
+          }
+          wave_sync();
+        }
+        const int c = min(e0 + w, ready);
+        const bool past = __float_as_int(pb[c & (kRing - 1)][rl].w) >= J1;
+        const int f = min8(past ? c : INT_MAX);
+        const bool none = f == INT_MAX;        // all kWin pairs have ended
+        if (act) e0 = none ? e0 + kWin : f;
+        const bool dry = act && !none && e0 == ready;
+        if (dry && ready == n) act = false;
+        if (ballot(dry && act)) {
+          if (dry && act) stage();
+          wave_sync();
+        } else if (!ballot(act && none)) {
+          break;
+        }
+      }
+      J = max(J1, __float_as_int(pa[e0 & (kRing - 1)][rl].w));
+    }
+    const int j_end = max8(j_last);
+    if (valid && w == 0) {
+      if (bg) {   // composite over the background: I + (1 - A) B
+        const float b = 1.0f - T;
+        I0 = fmaf(b, bg[3 * ray], I0);
+        I1 = fmaf(b, bg[3 * ray + 1], I1);
+        I2 = fmaf(b, bg[3 * ray + 2], I2);
+      }
+      rgba[ray] = make_float4(I0, I1, I2, T);
+      if (aux) aux[ray] = mvp_ray_aux{j_end, t_prev};
+    }
+  }
+  if (counters && ballot(n_pj != 0)) {
+    const unsigned long long c[5] = {wave_sum_u64(n_ray), wave_sum_u64(n_prim), wave_sum_u64(n_cell),
+                                     wave_sum_u64(n_pj), wave_sum_u64(n_pj)};
+    if (lane == 0) {
+#pragma unroll
+      for (int i = 0; i < 5; ++i) atomicAdd(counter_slot(counters) + i, c[i]);
     }
   }
 }
 
 hipError_t launch_march_fwd(const AccelView &av, const mvp_prims &p, const float *bg, float *rgba,
-                            mvp_ray_aux *aux, unsigned long long *counters, hipStream_t s,
-                            const PairsOut *build_pairs) {
-  const int ntile = av.V * av.tiles_x * av.tiles_y;
-  if (ntile == 0) return hipSuccess;
+                            mvp_ray_aux *aux, unsigned long long *counters, hipStream_t s) {
+  const int64_t ntile = (int64_t)av.V * av.tiles_x * av.tiles_y;
+  if (ntile == 0 || av.n_slots == 0) return hipSuccess;
+  const int64_t units = av.tile_rays ? (av.n_slots + kRaysPerWave - 1) / kRaysPerWave : march_units(av);
+  const int grid = (int)std::min<int64_t>((units + kXcd - 1) / kXcd * kXcd, 1 << 22);   // a multiple of kXcd
   const bool fade = av.fade_alpha > 0.f;
   const size_t shm = fade ? (size_t)av.M * sizeof(float) : 0;
-  const PairsOut po = build_pairs ? *build_pairs : PairsOut{};
-#define MVP_FWD(B, F, P)                                                                                     \
-  hipLaunchKernelGGL((k_march_fwd<B, F, P>), dim3(xcd_grid(ntile)), dim3(kTileThreads), shm, s, av, p.payload, \
-                     bg, (float4 *)rgba, aux, counters, po)
-#define MVP_FWD_P(B, F)                  \
-  do {                                   \
-    if (build_pairs) MVP_FWD(B, F, true); \
-    else MVP_FWD(B, F, false);           \
+#define MVP_FWD(B, F, S)                                                                                  \
+  hipLaunchKernelGGL((k_march_fwd<B, F, S>), dim3(grid), dim3(kWave), shm, s, av,                       \
+                     (const char *)p.payload, bg, (float4 *)rgba, aux, counters, units)
+#define MVP_FWD_S(B, F)               \
+  do {                                \
+    if (av.combine) MVP_FWD(B, F, true); \
+    else MVP_FWD(B, F, false);        \
   } while (0)
   if (p.payload_dtype == MVP_BF16) {
-    if (fade) MVP_FWD_P(true, true); else MVP_FWD_P(true, false);
+    if (fade) MVP_FWD_S(true, true); else MVP_FWD_S(true, false);
   } else {
-    if (fade) MVP_FWD_P(false, true); else MVP_FWD_P(false, false);
+    if (fade) MVP_FWD_S(false, true); else MVP_FWD_S(false, false);
   }
-#undef MVP_FWD_P
+#undef MVP_FWD_S
 #undef MVP_FWD
   return hipGetLastError();
 }
@@ -663,7 +792,7 @@ __global__ __launch_bounds__(256) void k_bwd_rays(AccelView av, const void *__re
     // the forward visited them
     const float tau = (float)ax.j_end * av.step;
     const int tile = slot_tile(av, r);
-    const Frames fr{nullptr, av.tile_off[tile]};
+    const uint64_t lb = av.tile_off[tile];
     int v, px, py;
     slot_pixel(av, r, &v, &px, &py);
     float d[3];
@@ -677,7 +806,7 @@ __global__ __launch_bounds__(256) void k_bwd_rays(AccelView av, const void *__re
       for (int i = next_by_id(av, seg, stride, n, ax.j_end, last); i < n; i = next_by_id(av, seg, stride, n, ax.j_end, last)) {
         const int4 pq = av.pr[seg + i * stride];
         float4 A, B;
-        fr.local(av, pq.z, Dir{d, 1}, A, B);
+        entry_ray(av, lb + (uint64_t)pq.z, d, A, B);
         const float4 s = sample_pair<BF16, FADE>(av, pay, s_fade, A, B, tau);
         const float Tn = T + s.w * av.step;
         last = pq.w;
@@ -704,7 +833,7 @@ __global__ __launch_bounds__(256) void k_bwd_rays(AccelView av, const void *__re
         for (int k = 0; k < kB; ++k) {
           if (q[k].x > ax.j_end || q[k].y < ax.j_end) continue;
           float4 A, B;
-          fr.local(av, q[k].z, Dir{d, 1}, A, B);
+          entry_ray(av, lb + (uint64_t)q[k].z, d, A, B);
           const float4 s = sample_pair<BF16, FADE>(av, pay, s_fade, A, B, tau);
           sig += s.w;
           c0 = fmaf(s.w, s.x, c0);
@@ -847,8 +976,7 @@ __device__ __forceinline__ void bwd_pair(const AccelView &av, const float *__res
   float d[3];
   pixel_ray(av.cams[rv], px, py, d);
   float4 A, B;   // the pair's local ray, from the frame of its culling-list entry gent
-  const Frames fr{nullptr, gent};
-  fr.local(av, 0, Dir{d, 1}, A, B);
+  entry_ray(av, gent, d, A, B);
   const mvp_ray_aux ax = aux[ray];
   const float4 g = grad_rgba[ray];
   const RayConst rcv = rc[ray];
@@ -1393,7 +1521,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES))
                                      wave_sum_u64(n_nz)};
     if (lane == 0 && (c[0] | c[1] | c[3])) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) atomicAdd(&counters[kCntBwdVisit + i], c[i]);
+      for (int i = 0; i < 4; ++i) atomicAdd(counter_slot(counters) + kCntBwdVisit + i, c[i]);
     }
   }
 }
@@ -1412,7 +1540,7 @@ hipError_t launch_march_bwd(const AccelView &av, const mvp_prims &p, int64_t n_i
                             hipEvent_t t0, hipEvent_t t1) {
   const size_t R = (size_t)av.n_slots;
   if (counters) {
-    const hipError_t ez = launch_zero_u64((uint64_t *)counters + kCntBwdVisit, 4, s);
+    const hipError_t ez = launch_zero_counters(counters, kCntBwdVisit, 4, s);
     if (ez != hipSuccess) return ez;
   }
   if (R == 0) return hipSuccess;

@@ -1,7 +1,5 @@
 // The per-ray pair lists of one screen tile: the canonical FP32 geometry
-// (slab test, sample intervals) and the per-tile pairs pass, shared by the
-// build's pairs kernel and by the forward march, which can build a tile's
-// pairs itself just before marching them.
+// (slab test, sample intervals) and the per-tile pairs pass of the pairs kernel.
 //
 // Built with -ffp-contract=off and IEEE division/square root: every written
 // float operation below is exactly one binary32 operation, so the hit
@@ -326,7 +324,7 @@ __device__ inline void tile_pairs(const AccelView &av, int tile, const PairsOut 
     o.ray_nj[ray] = make_int2(i, i ? (nw ? o.pr[seg].x : tb[0].x) : INT_MAX);
   }
   const unsigned long long c = wave_sum_u64((unsigned long long)i);
-  if (lane == 0 && c) atomicAdd(o.n_pairs, c);
+  if (lane == 0 && c) atomicAdd(counter_slot(o.counters) + kCntPairs, c);
 }
 
 

@@ -66,7 +66,7 @@ class Server {
     bool waiting = false;              // its build waits for memory (mu_)
     std::atomic<bool> finished{false};
     double t_finish = 0;
-    uint64_t *h_counts = nullptr;      // pinned: the forward's ray- and prim-sample counts
+    uint64_t *h_counts = nullptr;      // pinned: a copy of the forward's counters
     uint64_t ray_samples = 0, prim_samples = 0;
     uint64_t ticket = 0;
     mvp_accel *accel = nullptr;
@@ -141,8 +141,8 @@ void Server::host_done(void *p) {
   Slot *s = (Slot *)p;
   s->t_finish = now_s();
   // the copy of the counts was enqueued before this callback on the same stream
-  s->ray_samples = s->h_counts ? s->h_counts[0] : 0;
-  s->prim_samples = s->h_counts ? s->h_counts[1] : 0;
+  s->ray_samples = s->h_counts ? sum_counter(s->h_counts, kCntRaySamples) : 0;
+  s->prim_samples = s->h_counts ? sum_counter(s->h_counts, kCntPrimSamples) : 0;
   s->finished.store(true);
   Server *srv = s->srv;
   { std::lock_guard<std::mutex> g(srv->mu_); }
@@ -247,12 +247,13 @@ void Server::work(Slot &slot) {
                                  /*for_backward=*/false);
     if (st == MVP_OK) {
       slot.accel = a;
-      hipError_t e = launch_zero_u64((uint64_t *)a->counters, kCntFwdPab + 1, slot.stream);
+      hipError_t e = launch_zero_counters(a->counters, 0, kCntFwdPab + 1, slot.stream);
+      if (e == hipSuccess && a->pairs_pending.exchange(false)) e = launch_pairs(a->view(prims.M), a->po, slot.stream);
       if (e == hipSuccess)
-        e = launch_march_fwd(a->view(prims.M), prims, nullptr, req.rgba_out, nullptr, a->counters, slot.stream,
-                             a->pairs_pending.exchange(false) ? &a->po : nullptr);
-      if (e == hipSuccess && slot.h_counts)   // counters [0] ray-samples, [1] prim-samples of the forward
-        e = hipMemcpyAsync(slot.h_counts, a->counters, 2 * sizeof(uint64_t), hipMemcpyDeviceToHost, slot.stream);
+        e = launch_march_fwd(a->view(prims.M), prims, nullptr, req.rgba_out, nullptr, a->counters, slot.stream);
+      if (e == hipSuccess && slot.h_counts)
+        e = hipMemcpyAsync(slot.h_counts, a->counters, kCntSlots * kCntStride * sizeof(uint64_t), hipMemcpyDeviceToHost,
+                           slot.stream);
       if (e == hipSuccess) e = hipLaunchHostFunc(slot.stream, &Server::host_done, &slot);
       if (e != hipSuccess) {
         set_error("launch failed: %s", hipGetErrorString(e));
