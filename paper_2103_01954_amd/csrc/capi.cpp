@@ -455,20 +455,25 @@ mvp_status build_accel(mvp_ctx *ctx, const mvp_prims *prims, const mvp_camera *c
   // culling lists: rectangles, tile counts, offsets; pair capacities; one
   // stream synchronisation for the sizes
   MVP_HIP(launch_zero_u32(tile_cnt, ntile, s));
-  MVP_HIP(launch_prep(*prims, av, a->xf, rect, depth, tile_cnt, s));
+  MVP_HIP(launch_prep(*prims, av, a->xf, rect, depth, tile_cnt, a->counters, s));
   MVP_HIP(launch_scan_u32_u64(tile_cnt, a->tile_off, ntile, scratch, s));
   MVP_HIP(launch_tile_capacity(tile_cnt, rcnt, ntile, cap, s));
   MVP_HIP(launch_scan_u32_u64(cap, a->pair_base, ntile, scratch, s));
-  // the three sizes gathered into one small device block, then one copy down
+  // the sizes gathered into one small device block, then one copy down
   uint64_t *dsz = (uint64_t *)a->counters + kCntSizes;
   MVP_HIP(launch_gather_sizes(a->tile_off + ntile, a->pair_base + ntile, flag, dsz, s));
-  uint64_t host_sz[3] = {0, 0, 0};
+  uint64_t host_sz[5] = {0, 0, 0, 0, 0};
   uint64_t *hsz = pin.p ? (uint64_t *)pin.p : host_sz;
-  MVP_HIP(hipMemcpyAsync(hsz, dsz, 3 * sizeof(uint64_t), hipMemcpyDeviceToHost, s));
+  MVP_HIP(hipMemcpyAsync(hsz, dsz, 5 * sizeof(uint64_t), hipMemcpyDeviceToHost, s));
   MVP_HIP(hipStreamSynchronize(s));
   pin.synced = true;
   const uint64_t n_tile_pairs = hsz[0], capacity = hsz[1];
   const uint32_t flag_h = (uint32_t)hsz[2];
+  {
+    const uint32_t b0 = (uint32_t)hsz[3], b1 = (uint32_t)hsz[4];
+    memcpy(&a->max_dist_ratio, &b0, 4);
+    memcpy(&a->max_inv_scale, &b1, 4);
+  }
   if (flag_h & 1u) { set_error("a ray pixel id is outside [0, n_views*height*width)"); return MVP_ERR_INVALID; }
   if (flag_h & 2u) { set_error("more than 256 rays in one 16x16 tile (repeated pixel ids)"); return MVP_ERR_INVALID; }
   if (capacity >= (uint64_t)1 << 32) {

@@ -222,8 +222,32 @@ __global__ __launch_bounds__(256) void k_prep(int N, const float *__restrict__ p
                                               const float *__restrict__ rot,
                                               const float *__restrict__ scale, AccelView av,
                                               float4 *__restrict__ xf, int4 *__restrict__ rect,
-                                              uint32_t *__restrict__ depth, uint32_t *__restrict__ tile_cnt) {
+                                              uint32_t *__restrict__ depth, uint32_t *__restrict__ tile_cnt,
+                                              unsigned long long *__restrict__ counters) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
+  // the largest 1 / s and distance / s over the boxes (for the backward)
+  float inv_s = 0.f, far_s = 0.f;
+  if (k < N) {
+    inv_s = 1.0f / fminf(scale[3 * (size_t)k], fminf(scale[3 * (size_t)k + 1], scale[3 * (size_t)k + 2]));
+    for (int v = 0; v < av.V; ++v) {
+      float d2 = 0.f;
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        const float r = pos[3 * (size_t)k + i] - av.cams[v].o[i];
+        d2 += r * r;
+      }
+      far_s = fmaxf(far_s, sqrtf(d2) * inv_s);
+    }
+  }
+#pragma unroll
+  for (int d = kWave / 2; d > 0; d >>= 1) {
+    inv_s = fmaxf(inv_s, __shfl_xor(inv_s, d, kWave));
+    far_s = fmaxf(far_s, __shfl_xor(far_s, d, kWave));
+  }
+  if ((threadIdx.x & (kWave - 1)) == 0 && k < N) {   // non-negative floats order like their bits
+    atomicMax(&counters[kCntSizes + 3], (unsigned long long)__float_as_uint(far_s));
+    atomicMax(&counters[kCntSizes + 4], (unsigned long long)__float_as_uint(inv_s));
+  }
   if (k >= N) return;
   float R[9], s[3], t[3];
 #pragma unroll
@@ -315,10 +339,10 @@ __global__ __launch_bounds__(256) void k_prep(int N, const float *__restrict__ p
 }
 
 hipError_t launch_prep(const mvp_prims &p, const AccelView &av, float4 *xf, int4 *rect, uint32_t *depth,
-                       uint32_t *tile_cnt, hipStream_t s) {
+                       uint32_t *tile_cnt, unsigned long long *counters, hipStream_t s) {
   if (p.n_prim == 0) return hipSuccess;
   hipLaunchKernelGGL(k_prep, dim3((p.n_prim + 255) / 256), dim3(256), 0, s, p.n_prim, p.pos, p.rot,
-                     p.scale, av, xf, rect, depth, tile_cnt);
+                     p.scale, av, xf, rect, depth, tile_cnt, counters);
   return hipGetLastError();
 }
 

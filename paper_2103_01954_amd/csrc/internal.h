@@ -79,6 +79,7 @@ struct AccelView {
   float fade_alpha, fade_beta; // opacity fade window (alpha == 0: none)
   int32_t combine;             // 0: sum rule, 1: sequential in primitive-id order
   int32_t item_entries;        // culling-list entries per backward work item
+  float max_dist_ratio, max_inv_scale;   // over the boxes: distance / smallest half extent, 1 / half extent
   const DevCam *cams;          // [V]
   const float4 *xf;            // [N*3]: rows of A = diag(1/s) R^T, .w = t
   const uint64_t *tile_off;    // [V*T+1]
@@ -226,8 +227,9 @@ enum : int {
   kCntBwdRuns = 7,      // backward: cell runs (voxel-corner sets loaded)
   kCntBwdFlush = 8,     // backward: non-zero gradient values added to device memory
   kCntPairs = 9,        // build: (ray, primitive) pairs with at least one sample
-  kCntSizes = 10,       // build: culling-list entries, pair capacity, ray-subset flags (3 words)
-  kNumCounters = 13
+  kCntSizes = 10,       // build: culling-list entries, pair capacity, ray-subset flags (3 words),
+                        // then max |t - o| / min s and max 1 / s over the boxes (float bits, 2 words)
+  kNumCounters = 15
 };
 constexpr int kCntSlots = 64, kCntStride = 16;   // counter c of copy s at [s * kCntStride + c]
 __device__ __forceinline__ unsigned long long *counter_slot(unsigned long long *counters) {
@@ -251,7 +253,7 @@ hipError_t launch_scan_u32_u64(const uint32_t *in, uint64_t *out, size_t n, void
 // per primitive: A rows and t (xf), per view its tile rectangle (rect) and an
 // order key along the view's rays (depth); counts tile entries
 hipError_t launch_prep(const mvp_prims &p, const AccelView &av, float4 *xf, int4 *rect, uint32_t *depth,
-                       uint32_t *tile_cnt, hipStream_t s);
+                       uint32_t *tile_cnt, unsigned long long *counters, hipStream_t s);
 hipError_t launch_tile_fill(const AccelView &av, const int4 *rect, uint32_t *cursor,
                             uint32_t *tile_list, hipStream_t s);
 // transpose the culling lists (count per primitive, then place each entry
