@@ -987,6 +987,42 @@ __device__ __forceinline__ LineFn along(const float (&F)[8], float x, float y, f
 // Longest run taken at once (a longer one is taken in parts).
 constexpr int kRunMax = 64;
 
+// Cell layers [z0, z1) of a primitive that a work item handles: all of them,
+// or one slab of a payload whose gradient does not fit the LDS.
+struct Slab {
+  int z0, z1;
+};
+
+// The samples of [lo, hi] of a pair whose cells lie in the slab (z of the local
+// ray: a, b).  The layer of a sample is locate's, and monotone along the ray:
+// the ends are predicted, then settled with locate's own arithmetic, so that
+// every sample belongs to exactly one slab.
+__device__ __forceinline__ void clip_to_slab(const Slab &sl, float a, float b, float dt, int M, float hM, int &lo,
+                                             int &hi) {
+  const float top = (float)(M - 2);
+  auto layer = [&](int j) {
+    const float y = fmaf((float)j * dt, b, a);
+    return (int)fminf(floorf(fmaf(fminf(fmaxf(y, -1.0f), 1.0f), hM, hM)), top);
+  };
+  if (lo > hi) return;
+  const bool up = b >= 0.f;
+  // first sample at or past the entry face, last one before the exit face
+  const float step = b * hM * dt;
+  const float is = fabsf(step) > 1e-12f ? 1.0f / step : 0.f;
+  const float u0 = fmaf(a, hM, hM);
+  const float te = ((float)(up ? sl.z0 : sl.z1) - u0) * is, tx = ((float)(up ? sl.z1 : sl.z0) - u0) * is;
+  auto in = [&](int j) { return up ? layer(j) >= sl.z0 : layer(j) < sl.z1; };      // past the entry face
+  auto out = [&](int j) { return up ? layer(j) >= sl.z1 : layer(j) < sl.z0; };     // past the exit face
+  int e = (int)fminf(fmaxf(is != 0.f ? ceilf(te) : (float)lo, (float)lo), (float)hi);
+  while (e > lo && in(e - 1)) --e;
+  while (e <= hi && !in(e)) ++e;
+  int x = (int)fminf(fmaxf(is != 0.f ? floorf(tx) : (float)hi, (float)lo), (float)hi);
+  while (x < hi && !out(x + 1)) ++x;
+  while (x >= lo && out(x)) --x;
+  lo = e;
+  hi = x;
+}
+
 // Replay one (ray, primitive k) pair backward: channel adjoints to the 8
 // voxel corners (registers over a run of samples in one cell, then gdst:
 // the LDS copy of k's gradient or device memory) and the pair's pose sums
@@ -1002,17 +1038,17 @@ constexpr int kRunMax = 64;
 // 8^3, four 1024^2 views (5 samples per run): 6.5 -> 4.2 ms; 512 x 16^3 at
 // 667 x 1024: 4.4 -> 1.9 ms.  At 2 samples per run the two are equal (32768 x
 // 16^3 at 2 x 2048^2: 26.8 and 27.0 ms): see backward_by_runs.
-template <bool BF16, bool LDS_ACC, bool FADE, bool RUNS, bool PREFETCH, typename GAcc>
+template <bool BF16, bool LDS_ACC, bool FADE, bool RUNS, bool SLABS, bool PREFETCH, typename GAcc>
 __device__ __forceinline__ void bwd_pair(const AccelView &av, const char *__restrict__ payk,
                                          const mvp_ray_aux *__restrict__ aux, const float4 *__restrict__ grad_rgba,
                                          const RayConst *__restrict__ rc, const uint2 rec, uint64_t gent, int tile,
-                                         int k, const float (&t)[3], GAcc *gdst, const LdsMap &lm, float fxs,
+                                         int k, const float (&t)[3], const Slab &slab, GAcc *gdst, const LdsMap &lm, float fxs,
                                          const float *s_fade, bool pose,
                                          float (&P)[12], uint32_t &runs) {
   const int M = av.M;
   const float hM = 0.5f * (float)(M - 1);
   const float dt = av.step;
-  const int2 jr = make_int2((int)(rec.x & 0xffffffu), (int)rec.y);
+  int2 jr = make_int2((int)(rec.x & 0xffffffu), (int)rec.y);
   size_t ray;
   int rv, px, py;
   (void)tile_ray(av, tile, (int)(rec.x >> 24), &ray, &rv, &px, &py);
@@ -1028,7 +1064,8 @@ __device__ __forceinline__ void bwd_pair(const AccelView &av, const char *__rest
   // (primitives before it are ordinary steps, those after it add nothing)
   const bool seq = av.combine != 0;
   const bool clamped = ax.t_prev >= 0.f && (!seq || rcv.kstar >= 0);
-  const int jh = min(jr.y, ax.j_end);
+  int jh = min(jr.y, ax.j_end);
+  if (SLABS) clip_to_slab(slab, A.z, B.z, dt, M, hM, jr.x, jh);
   float G0 = 0.f, G1 = 0.f, G2 = 0.f, H0 = 0.f, H1 = 0.f, H2 = 0.f;
   float4 cv[8];
   float wq[8];
@@ -1228,7 +1265,7 @@ __device__ __forceinline__ void bwd_pair(const AccelView &av, const char *__rest
           acc[q8][3] = b3[q8];
         }
         const size_t fc = LDS_ACC ? (size_t)((unsigned)ci0 + __umul24((unsigned)ci1, (unsigned)lm.sy) +
-                                             __umul24((unsigned)ci2, (unsigned)lm.sz))
+                                             __umul24((unsigned)(SLABS ? ci2 - slab.z0 : ci2), (unsigned)lm.sz))
                                   : (size_t)cell;
         flush_cell<LDS_ACC, FADE>(gdst, fc, M, lm, acc, wq, m, fxs);
       }
@@ -1346,7 +1383,7 @@ __device__ __forceinline__ void bwd_pair(const AccelView &av, const char *__rest
       }
       if (gdst) {
         const size_t fc = LDS_ACC ? (size_t)((unsigned)ci0 + __umul24((unsigned)ci1, (unsigned)lm.sy) +
-                                             __umul24((unsigned)ci2, (unsigned)lm.sz))
+                                             __umul24((unsigned)(SLABS ? ci2 - slab.z0 : ci2), (unsigned)lm.sz))
                                   : (size_t)cell;
         flush_cell<LDS_ACC, FADE>(gdst, fc, M, lm, acc, wq, m, fxs);
       }
@@ -1409,17 +1446,26 @@ __device__ __forceinline__ float nan_max(float a, float b) {
   return (a == a && b == b) ? fmaxf(a, b) : __builtin_nanf("");
 }
 
+template <bool SLABS>
 __device__ __forceinline__ int pair_len(const AccelView &av, const mvp_ray_aux *__restrict__ aux,
-                                        const RayBound *__restrict__ rbd, const uint2 rec, int tile, float &bound) {
-  const int2 jr = make_int2((int)(rec.x & 0xffffffu), (int)rec.y);
+                                        const RayBound *__restrict__ rbd, const uint2 rec, uint64_t gent, int tile,
+                                        const Slab &slab, float &bound) {
+  int lo = (int)(rec.x & 0xffffffu);
   size_t ray;
   int rv, px, py;
   (void)tile_ray(av, tile, (int)(rec.x >> 24), &ray, &rv, &px, &py);
   const int je = aux[ray].j_end;
-  const int n = max(0, min(jr.y, je) - jr.x + 1);
+  int hi = min((int)rec.y, je);
+  if (SLABS && lo <= hi) {
+    float d[3];
+    pixel_ray(av.cams[rv], px, py, d);
+    const float4 f = av.ef[3 * gent + 2];
+    clip_to_slab(slab, f.w, row_dot(f.x, f.y, f.z, d), av.step, av.M, 0.5f * (float)(av.M - 1), lo, hi);
+  }
+  const int n = max(0, hi - lo + 1);
   if (n > 0) {
     const RayBound rb = rbd[ray];
-    const float b = (float)n * rb.per_sample + (jr.y >= je ? rb.clamp : 0.f);
+    const float b = (float)n * rb.per_sample + (hi >= je ? rb.clamp : 0.f);
     bound = nan_max(bound, b);
   }
   return n;
@@ -1454,11 +1500,11 @@ __device__ __forceinline__ int len_bucket(int n) { return n < 32 ? n : min(kLenB
 // LDS gradient leaves room for that many workgroups per CU.  THREADS is the
 // workgroup size: 512 when the LDS gradient leaves room for only one
 // workgroup per CU, so that the CU still runs two waves per SIMD.
-template <bool BF16, bool LDS_ACC, bool FADE, bool RUNS, int WAVES, int THREADS>
+template <bool BF16, bool LDS_ACC, bool FADE, bool RUNS, int WAVES, int THREADS, bool SLABS = false>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES))) void k_bwd_items(
     AccelView av, const float *__restrict__ rot, const float *__restrict__ scale, const void *__restrict__ pay,
     const mvp_ray_aux *__restrict__ aux, const float4 *__restrict__ grad_rgba, const RayConst *__restrict__ rc,
-    const RayBound *__restrict__ rbd, BwdOut out, uint32_t sort_cap, int padded,
+    const RayBound *__restrict__ rbd, BwdOut out, uint32_t sort_cap, int padded, int slab_cells,
     unsigned long long *__restrict__ counters) {
   // loads of this thread: pairs visited by the ordering / bound pass, pairs
   // replayed, their cell runs (one voxel-corner set each), and the non-zero
@@ -1484,8 +1530,10 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES))
   __shared__ int s_prim, s_pos;
   const int M = av.M;
   const size_t M3 = (size_t)M * M * M;
-  const int nacc = (int)(M3 * 4);                 // gradient values of one primitive
-  const LdsMap lm = lds_map(M, padded != 0);
+  // SLABS: an item is taken once per slab of slab_cells cell layers, whose voxel
+  // layers are the LDS copy
+  const uint32_t n_slab = SLABS ? (uint32_t)((M - 2 + slab_cells) / slab_cells) : 1u;
+  const LdsMap lm = SLABS ? LdsMap{M, M * M, M * M * (slab_cells + 1) + 1} : lds_map(M, padded != 0);
   const int nlds = 4 * lm.plane;                  // their planar LDS copy
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const bool pose = out.pos || out.rot || out.scale;
@@ -1497,8 +1545,14 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES))
     fill_fade(s_fade, M, av.fade_alpha, av.fade_beta);
     __syncthreads();
   }
-  const uint64_t n_items = av.item_off[av.N];
-  for (uint64_t it = blockIdx.x; it < n_items; it += gridDim.x) {
+  const uint64_t n_items = av.item_off[av.N] * n_slab;
+  for (uint64_t is = blockIdx.x; is < n_items; is += gridDim.x) {
+    const uint64_t it = SLABS ? is / n_slab : is;
+    Slab slab{0, M - 1};
+    if (SLABS) {
+      slab.z0 = (int)(is - it * n_slab) * slab_cells;
+      slab.z1 = min(slab.z0 + slab_cells, M - 1);
+    }
     if (threadIdx.x == 0) {   // primitive of the item: the p-th in item order, last p with item_off[p] <= it
       int lo = 0, hi = av.N - 1;
       while (lo < hi) {
@@ -1583,7 +1637,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES))
       __syncthreads();
       for (uint32_t i = c0, q = q0; i < c1; ++i) {
         while (s_pre[q + 1] <= i) ++q;
-        const int n = pair_len(av, aux, rbd, av.ent_rec[s_start[q] + (i - s_pre[q])], s_tile[q >> 2], bound);
+        const int n = pair_len<SLABS>(av, aux, rbd, av.ent_rec[s_start[q] + (i - s_pre[q])], s_gent[q >> 2], s_tile[q >> 2], slab, bound);
         ++n_visit;
         const int b = n > 0 ? len_bucket(n) : 0xff;
         s_pcls[i] = (uint8_t)b;
@@ -1651,7 +1705,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES))
           if (s_pre[mid] <= i) q = mid; else hi = mid - 1;
         }
         const uint2 rec = av.ent_rec[s_start[q] + (i - s_pre[q])];
-        bwd_pair<BF16, LDS_ACC, FADE, RUNS, WAVES == 1>(av, payk, aux, grad_rgba, rc, rec, s_gent[q >> 2], s_tile[q >> 2], k, t, gdst,
+        bwd_pair<BF16, LDS_ACC, FADE, RUNS, SLABS, WAVES == 1>(av, payk, aux, grad_rgba, rc, rec, s_gent[q >> 2], s_tile[q >> 2], k, t, slab, gdst,
                                       lm, fscale, s_fade, pose, P, n_run);
         ++n_rep;
       }
@@ -1676,7 +1730,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES))
       if (LDS_ACC && out.pay) {   // the item's bound, for the fixed-point scale
         for (uint32_t i = i0, q = q0; i < iend; i += stride) {
           while (s_pre[q + 1] <= i) ++q;
-          (void)pair_len(av, aux, rbd, av.ent_rec[s_start[q] + (i - s_pre[q])], s_tile[q >> 2], bound);
+          (void)pair_len<SLABS>(av, aux, rbd, av.ent_rec[s_start[q] + (i - s_pre[q])], s_gent[q >> 2], s_tile[q >> 2], slab, bound);
           ++n_visit;
         }
 #pragma unroll
@@ -1691,7 +1745,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES))
       for (uint32_t i = i0, q = q0; i < iend; i += stride) {
         while (s_pre[q + 1] <= i) ++q;
         const uint2 rec = av.ent_rec[s_start[q] + (i - s_pre[q])];
-        bwd_pair<BF16, LDS_ACC, FADE, RUNS, WAVES == 1>(av, payk, aux, grad_rgba, rc, rec, s_gent[q >> 2], s_tile[q >> 2], k, t, gdst,
+        bwd_pair<BF16, LDS_ACC, FADE, RUNS, SLABS, WAVES == 1>(av, payk, aux, grad_rgba, rc, rec, s_gent[q >> 2], s_tile[q >> 2], k, t, slab, gdst,
                                       lm, fscale, s_fade, pose, P, n_run);
         ++n_rep;
       }
@@ -1725,7 +1779,8 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES))
       }
     }
     if (LDS_ACC && out.pay && total > 0) {
-      float *dst = out.pay + M3 * 4 * (size_t)k;
+      float *dst = out.pay + (M3 * (size_t)k + (size_t)slab.z0 * M * M) * 4;
+      const int nacc = (slab.z1 - slab.z0 + 1) * M * M * 4;   // gradient values of the slab (shared layers: added by both)
       const bool ok = fscale > 0.0f;
       const float inv = ok ? 1.0f / fscale : __builtin_nanf("");   // exact: a power of two
       for (int i = threadIdx.x; i < nacc; i += THREADS) {   // device order: voxel i/4, channel i%4
@@ -1749,23 +1804,29 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES))
   }
 }
 
-// The work-item kernel for 3 waves per SIMD (w3), 512-thread workgroups
-// (wide_wg) or neither.
+// The work-item kernel for 3 waves per SIMD, 2 workgroups per CU, one of 512
+// threads, or one of 512 threads in slabs.
+enum class BwdShape { kThree, kTwo, kOne, kSlabs };
 typedef void (*BwdItemsFn)(AccelView, const float *, const float *, const void *, const mvp_ray_aux *, const float4 *,
-                           const RayConst *, const RayBound *, BwdOut, uint32_t, int, unsigned long long *);
+                           const RayConst *, const RayBound *, BwdOut, uint32_t, int, int, unsigned long long *);
 template <bool B, bool L, bool F, bool R>
-static BwdItemsFn bwd_items_fn(bool w3, bool wide_wg) {
-  return w3 ? k_bwd_items<B, L, F, R, 3, kTileThreads>
-            : (wide_wg ? k_bwd_items<B, L, F, R, 1, 2 * kTileThreads> : k_bwd_items<B, L, F, R, 1, kTileThreads>);
+static BwdItemsFn bwd_items_fn(BwdShape shape) {
+  if (shape == BwdShape::kThree) return k_bwd_items<B, L, F, R, 3, kTileThreads>;
+  if constexpr (L) {
+    if (shape == BwdShape::kSlabs) return k_bwd_items<B, L, F, R, 1, 2 * kTileThreads, true>;
+    if (shape == BwdShape::kOne) return k_bwd_items<B, L, F, R, 1, 2 * kTileThreads>;
+    return k_bwd_items<B, L, F, R, 1, kTileThreads>;
+  }
+  return nullptr;   // without the LDS copy three workgroups fit
 }
 template <bool B, bool L>
-static BwdItemsFn bwd_items_fn(bool fade, bool runs, bool w3, bool wide_wg) {
-  return fade ? (runs ? bwd_items_fn<B, L, true, true>(w3, wide_wg) : bwd_items_fn<B, L, true, false>(w3, wide_wg))
-              : (runs ? bwd_items_fn<B, L, false, true>(w3, wide_wg) : bwd_items_fn<B, L, false, false>(w3, wide_wg));
+static BwdItemsFn bwd_items_fn(bool fade, bool runs, BwdShape shape) {
+  return fade ? (runs ? bwd_items_fn<B, L, true, true>(shape) : bwd_items_fn<B, L, true, false>(shape))
+              : (runs ? bwd_items_fn<B, L, false, true>(shape) : bwd_items_fn<B, L, false, false>(shape));
 }
-static BwdItemsFn bwd_items_fn(bool bf16, bool lds, bool fade, bool runs, bool w3, bool wide_wg) {
-  return bf16 ? (lds ? bwd_items_fn<true, true>(fade, runs, w3, wide_wg) : bwd_items_fn<true, false>(fade, runs, w3, wide_wg))
-              : (lds ? bwd_items_fn<false, true>(fade, runs, w3, wide_wg) : bwd_items_fn<false, false>(fade, runs, w3, wide_wg));
+static BwdItemsFn bwd_items_fn(bool bf16, bool lds, bool fade, bool runs, BwdShape shape) {
+  return bf16 ? (lds ? bwd_items_fn<true, true>(fade, runs, shape) : bwd_items_fn<true, false>(fade, runs, shape))
+              : (lds ? bwd_items_fn<false, true>(fade, runs, shape) : bwd_items_fn<false, false>(fade, runs, shape));
 }
 
 // Whether the backward takes cell runs in closed form (bwd_pair).  Two lines:
@@ -1827,8 +1888,24 @@ hipError_t launch_march_bwd(const AccelView &av, const mvp_prims &p, int64_t n_i
   const size_t kStatic = 8192;   // static LDS of a 256-thread workgroup is under 8 KB (512: under 16 KB)
   auto lds_bytes = [&](bool pad) { return (size_t)lds_map(p.M, pad).plane * 4 * sizeof(unsigned long long); };
   const int padded = lds_bytes(true) + fade_shm + 2 * kStatic <= 160 * 1024 ? 1 : 0;
-  const size_t lds = lds_bytes(padded != 0);
-  const bool in_lds = g_pay && lds + fade_shm + 2 * kStatic <= 160 * 1024;
+  size_t lds = lds_bytes(padded != 0);
+  bool in_lds = g_pay && lds + fade_shm + 2 * kStatic <= 160 * 1024;
+  // A larger payload (up to 45^3): slabs of as many cell layers as fit beside
+  // the ordering buffer of 4096 pairs, each replaying the samples in it; every
+  // pair is set up once per slab (11 of 3 layers for 32^3), but adds to the LDS.
+  // Device atomics in their place, 32 per cell run, ran at 46 G/s: 64 x 32^3 at
+  // 667 x 1024 48.4 ms against 3.6.
+  int slab_cells = 0;
+  if (g_pay && !in_lds) {
+    const size_t layer = (size_t)p.M * p.M * 4 * sizeof(unsigned long long);
+    const int layers = (int)((160 * 1024 - 2 * kStatic - fade_shm - 4096 * 3 - 64) / layer);
+    if (layers >= 2) {
+      const int n_slab = (p.M - 2 + layers - 1) / (layers - 1);
+      slab_cells = (p.M - 2 + n_slab) / n_slab;
+      lds = ((size_t)p.M * p.M * (slab_cells + 1) + 1) * 4 * sizeof(unsigned long long);
+      in_lds = true;
+    }
+  }
   auto wgs_per_cu = [&](size_t grad) {
     for (int w = 3; w > 1; --w)
       if ((size_t)w * (grad + fade_shm + kStatic) <= 160 * 1024) return w;
@@ -1836,9 +1913,11 @@ hipError_t launch_march_bwd(const AccelView &av, const mvp_prims &p, int64_t n_i
   };
   // 3 waves per SIMD when 3 workgroups' LDS fits a CU; 512-thread workgroups
   // when only one does (16^3 payloads: 131 KB)
-  const bool w3 = !in_lds || wgs_per_cu(lds) >= 3;
-  bool wide_wg = in_lds && wgs_per_cu(lds) == 1;
-  const unsigned grid = (unsigned)std::min<int64_t>(n_items_max, 1 << 20);
+  const int wgs_fit = in_lds ? wgs_per_cu(lds) : 3;
+  BwdShape shape = slab_cells ? BwdShape::kSlabs : wgs_fit >= 3 ? BwdShape::kThree : wgs_fit == 2 ? BwdShape::kTwo : BwdShape::kOne;
+  auto wide = [&] { return shape == BwdShape::kOne || shape == BwdShape::kSlabs; };
+  const int64_t n_slab = slab_cells ? (p.M - 2 + slab_cells) / slab_cells : 1;
+  const unsigned grid = (unsigned)std::min<int64_t>(n_items_max * n_slab, 1 << 20);
   BwdOut out{g_pay, g_pos, g_rot, g_scale};
   size_t shm = (in_lds ? lds : 0) + fade_shm;
   // the pair-ordering buffer takes what is left of the LDS share of a
@@ -1846,29 +1925,30 @@ hipError_t launch_march_bwd(const AccelView &av, const mvp_prims &p, int64_t n_i
   // holds keep their pairs in list order)
   uint32_t sort_cap = 0;
   if (kSortPairs) {
-    const size_t wgs = w3 ? 3 : (shm + kStatic <= 80 * 1024 ? 2 : 1);
-    const size_t share = 160 * 1024 / wgs - (wide_wg ? 2 * kStatic : kStatic);
+    const size_t wgs = shape == BwdShape::kThree ? 3 : (shm + kStatic <= 80 * 1024 ? 2 : 1);
+    const size_t share = 160 * 1024 / wgs - (wide() ? 2 * kStatic : kStatic);
     const size_t room = share > shm ? (share - shm) / (sizeof(uint16_t) + 1) : 0;
     const size_t want = (size_t)av.item_entries * kTileThreads;
     sort_cap = (uint32_t)(std::min(room, want) / kTileThreads * kTileThreads);
     shm += (size_t)sort_cap * (sizeof(uint16_t) + 1);
   }
   const bool runs = backward_by_runs(av, p.M);
-  BwdItemsFn fn = bwd_items_fn(bf16, in_lds, fade, runs, w3, wide_wg);
+  BwdItemsFn fn = bwd_items_fn(bf16, in_lds, fade, runs, shape);
   if (shm > 64 * 1024) {
     // allow more than the default dynamic LDS per workgroup (gfx950 has 160 KB)
     if (hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) != hipSuccess) {
       (void)hipGetLastError();
       // gradients straight to device memory, pairs in list order
-      wide_wg = false;
+      shape = BwdShape::kThree;
+      slab_cells = 0;
       sort_cap = 0;
       shm = fade_shm;
-      fn = bwd_items_fn(bf16, false, fade, runs, w3, wide_wg);
+      fn = bwd_items_fn(bf16, false, fade, runs, shape);
     }
   }
   if (t0) (void)hipEventRecord(t0, s);
-  hipLaunchKernelGGL(fn, dim3(grid), dim3(wide_wg ? 2 * kTileThreads : kTileThreads), shm, s, av, p.rot, p.scale, p.payload,
-                     aux, (const float4 *)grad_rgba, rc, rbd, out, sort_cap, padded, counters);
+  hipLaunchKernelGGL(fn, dim3(grid), dim3(wide() ? 2 * kTileThreads : kTileThreads), shm, s, av, p.rot, p.scale, p.payload,
+                     aux, (const float4 *)grad_rgba, rc, rbd, out, sort_cap, padded, slab_cells, counters);
   e = hipGetLastError();
   if (t1) (void)hipEventRecord(t1, s);
   return e;
@@ -1876,7 +1956,9 @@ hipError_t launch_march_bwd(const AccelView &av, const mvp_prims &p, int64_t n_i
 
 // Entries per backward work item: 8^3 payloads flush small gradients, so
 // shorter items (more of them) balance better; larger payloads amortise the
-// per-item zeroing and flush of their LDS gradient over 64 entries.
-int backward_item_entries(int M) { return M <= 8 ? 32 : kItemEntries; }
+// per-item zeroing and flush of their LDS gradient over 64 entries; those taken
+// in slabs have few primitives and items of at most 4096 pairs, the ordering
+// buffer's size beside a slab.
+int backward_item_entries(int M) { return M <= 8 ? 32 : M <= 16 ? kItemEntries : 16; }
 
 }  // namespace mvp
