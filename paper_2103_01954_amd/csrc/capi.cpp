@@ -297,35 +297,29 @@ static mvp_status read_u64(const uint64_t *dev, uint64_t *host, hipStream_t s) {
 }
 
 // The transposed lists (primitive -> its culling-list entries) and the
-// backward work items, on the context's side stream after the build's kernels
-// (event `built`); they need only the sorted culling lists.  Launched once, by
-// the first forward after its own launch or by the first backward; `lists` is
-// recorded after them and the held temporaries are recycled after them.
-static mvp_status launch_lists(const mvp_accel *ac) {
+// backward work items; they need only the sorted culling lists.  Launched once,
+// by the first forward with per-ray state after its own launch or by the first
+// backward: on the context's side stream after the build's kernels (event
+// `built`), with `lists` recorded after them, or, where they take two short
+// kernels, on the caller's stream s, which saves the events between the streams.
+// The held temporaries are recycled after them.
+static mvp_status launch_lists(const mvp_accel *ac, hipStream_t s) {
   if (!ac->lists_pending.exchange(false)) return MVP_OK;
   mvp_accel *a = const_cast<mvp_accel *>(ac);
   mvp_ctx *ctx = a->ctx;
-  hipStream_t s2 = ctx->side;
-  const AccelView av = a->view(2);
-  const size_t N = (size_t)a->N;
-  const uint64_t ne = (uint64_t)a->n_tile_pairs;
-  hipError_t e = hipStreamWaitEvent(s2, a->built, 0);
-  if (e == hipSuccess) e = launch_zero_u32(a->prim_cnt, N, s2);
-  if (e == hipSuccess) e = launch_prim_entry_count(a->tile_list, ne, a->prim_cnt, s2);
-  if (e == hipSuccess) e = launch_scan_u32_u64(a->prim_cnt, a->prim_entry_off, N, a->scan_scratch, s2);
-  if (e == hipSuccess) e = launch_prim_entry_place(av, a->rect, ne, a->prim_entry_off, a->prim_entries, s2);
+  const bool beside = a->n_tile_pairs > 32768 || a->N > 8191;
+  hipStream_t s2 = beside ? ctx->side : s;
+  hipError_t e = beside ? hipStreamWaitEvent(s2, a->built, 0) : hipSuccess;
   if (e == hipSuccess)
-    e = launch_prim_order(a->rect, a->N, a->V, a->tiles_x, a->tiles_y, a->prim_key, a->prim_bcnt,
-                          a->prim_boff, a->scan_scratch, a->item_prim, s2);
-  if (e == hipSuccess)
-    e = launch_item_count(a->prim_entry_off, a->item_prim, a->N, a->item_entries, a->prim_cnt, s2);
-  if (e == hipSuccess) e = launch_scan_u32_u64(a->prim_cnt, a->item_off, N, a->scan_scratch, s2);
-  if (e == hipSuccess) e = hipEventRecord(a->lists, s2);
+    e = launch_prim_lists(a->view(2), a->rect, (uint64_t)a->n_tile_pairs, a->prim_cnt, a->prim_key, a->prim_bcnt,
+                          a->prim_boff, a->scan_scratch, a->prim_entry_off, a->prim_entries, a->item_prim, a->item_off, s2);
+  if (e == hipSuccess && beside) e = hipEventRecord(a->lists, s2);
   if (e != hipSuccess) {
     (void)hipStreamSynchronize(s2);
     a->lists_pending.store(true);   // a later call tries again
     MVP_HIP(e);
   }
+  a->lists_beside = beside;
   MVP_CHECK(ctx->arena.release_after(a->lists_temps, s2));
   a->lists_temps.clear();
   return MVP_OK;
@@ -387,9 +381,13 @@ mvp_status build_accel(mvp_ctx *ctx, const mvp_prims *prims, const mvp_camera *c
   MVP_HIP(hipSetDevice(ctx->device));
   Blocks keep{ctx, s}, temp{ctx, s}, ltmp{ctx, s};   // ltmp: temporaries the transposed lists read
   int4 *rect = nullptr;
-  uint32_t *tile_cnt = nullptr, *cap = nullptr, *rcnt = nullptr, *depth = nullptr;
+  uint32_t *tile_cnt = nullptr, *rcnt = nullptr, *depth = nullptr;
   uint8_t *scratch = nullptr;
-  const size_t sb = scan_scratch_bytes(std::max<size_t>(std::max<size_t>(ntile, (size_t)N), (size_t)kPrimBuckets));
+  const size_t sb = std::max(scan_scratch_bytes(std::max<size_t>(std::max<size_t>(ntile, (size_t)N), (size_t)kPrimBuckets)),
+                             tile_offsets_scratch_bytes(ntile));
+  // per-tile words cleared at the start: list lengths, list cursors, and for a
+  // ray subset its rays, their cursors and the flag
+  const size_t tile_words = rays ? 4 * ntile + 1 : 2 * ntile;
   if (admit) {
     const size_t base = n_views * sizeof(DevCam) + 3 * (size_t)N * 16 + 2 * (ntile + 1) * 8 + R * 16 + 16 +
                         kCntSlots * kCntStride * 8 + (size_t)n_views * N * 20 + 2 * ntile * 4 + sb + 10 * 256 +
@@ -405,8 +403,7 @@ mvp_status build_accel(mvp_ctx *ctx, const mvp_prims *prims, const mvp_camera *c
   MVP_CHECK(keep.get(&a->counters, kCntSlots * kCntStride));
   MVP_CHECK(ltmp.get(&rect, (size_t)n_views * N));
   MVP_CHECK(temp.get(&depth, (size_t)n_views * N));
-  MVP_CHECK(temp.get(&tile_cnt, ntile));
-  MVP_CHECK(temp.get(&cap, ntile));
+  MVP_CHECK(temp.get(&tile_cnt, tile_words));
   MVP_CHECK(ltmp.get(&scratch, sb));
   // cameras up and list sizes down through a pinned block (returned once the
   // build has synchronised, or on any early return)
@@ -421,50 +418,39 @@ mvp_status build_accel(mvp_ctx *ctx, const mvp_prims *prims, const mvp_camera *c
     }
   } pin{ctx->pinned, ctx->pinned.get(), s};
   const size_t cam_bytes = n_views * sizeof(DevCam);
-  if (pin.p && cam_bytes + 64 <= kPinnedBlock) {
-    memcpy((char *)pin.p + 64, a->cams_host.data(), cam_bytes);
-    MVP_HIP(hipMemcpyAsync(a->cams, (char *)pin.p + 64, cam_bytes, hipMemcpyHostToDevice, s));
-  } else {
-    MVP_HIP(hipMemcpyAsync(a->cams, a->cams_host.data(), cam_bytes, hipMemcpyHostToDevice, s));
-  }
-  MVP_HIP(launch_zero_u64((uint64_t *)a->counters, kCntSlots * kCntStride, s));
+  const bool pinned_cams = pin.p && cam_bytes + 64 <= kPinnedBlock;   // read by the first kernel
+  if (pinned_cams) memcpy((char *)pin.p + 64, a->cams_host.data(), cam_bytes);
+  else MVP_HIP(hipMemcpyAsync(a->cams, a->cams_host.data(), cam_bytes, hipMemcpyHostToDevice, s));
+  MVP_HIP(launch_build_init(tile_cnt, tile_words, a->counters, a->cams,
+                            pinned_cams ? (const DevCam *)((char *)pin.p + 64) : nullptr, n_views, s));
   uint32_t *flag = nullptr;
   if (rays) {
     // ray subset: a private copy of the pixel ids, binned into screen tiles
     MVP_CHECK(keep.get(&a->ray_pix, R ? R : 1));
     MVP_CHECK(keep.get(&a->tile_ray_off, ntile + 1));
     MVP_CHECK(keep.get(&a->tile_rays, R ? R : 1));
-    MVP_CHECK(temp.get(&rcnt, ntile));
-    MVP_CHECK(temp.get(&flag, 1));
+    rcnt = tile_cnt + 2 * ntile;
+    flag = tile_cnt + 4 * ntile;
     if (R) MVP_HIP(hipMemcpyAsync(a->ray_pix, rays, R * sizeof(int64_t), hipMemcpyDeviceToDevice, s));
     AccelView rv = a->view(2);
-    MVP_HIP(launch_zero_u32(rcnt, ntile, s));
-    MVP_HIP(launch_zero_u32(flag, 1, s));
     MVP_HIP(launch_ray_bin(rv, rcnt, flag, s));
     MVP_HIP(launch_scan_u32_u64(rcnt, a->tile_ray_off, ntile, scratch, s));
     // rcnt keeps the per-tile ray counts (for the pair capacities); the fill
     // takes its own cursor
-    uint32_t *cursor = nullptr;
-    MVP_CHECK(temp.get(&cursor, ntile));
-    MVP_HIP(launch_zero_u32(cursor, ntile, s));
-    MVP_HIP(launch_ray_fill(rv, cursor, a->tile_rays, s));
+    MVP_HIP(launch_ray_fill(rv, tile_cnt + 3 * ntile, a->tile_rays, s));
     MVP_HIP(launch_segment_sort(a->tile_ray_off, a->tile_rays, (int64_t)ntile, nullptr, 0, 1, s));
   }
   AccelView av = a->view(2);
 
   // culling lists: rectangles, tile counts, offsets; pair capacities; one
   // stream synchronisation for the sizes
-  MVP_HIP(launch_zero_u32(tile_cnt, ntile, s));
   MVP_HIP(launch_prep(*prims, av, a->xf, rect, depth, tile_cnt, a->counters, s));
-  MVP_HIP(launch_scan_u32_u64(tile_cnt, a->tile_off, ntile, scratch, s));
-  MVP_HIP(launch_tile_capacity(tile_cnt, rcnt, ntile, cap, s));
-  MVP_HIP(launch_scan_u32_u64(cap, a->pair_base, ntile, scratch, s));
-  // the sizes gathered into one small device block, then one copy down
-  uint64_t *dsz = (uint64_t *)a->counters + kCntSizes;
-  MVP_HIP(launch_gather_sizes(a->tile_off + ntile, a->pair_base + ntile, flag, dsz, s));
   uint64_t host_sz[5] = {0, 0, 0, 0, 0};
-  uint64_t *hsz = pin.p ? (uint64_t *)pin.p : host_sz;
-  MVP_HIP(hipMemcpyAsync(hsz, dsz, 5 * sizeof(uint64_t), hipMemcpyDeviceToHost, s));
+  uint64_t *dsz = (uint64_t *)a->counters + kCntSizes;
+  uint64_t *hsz = pin.p ? (uint64_t *)pin.p : host_sz;   // the pinned block is written by the last kernel itself
+  MVP_HIP(launch_tile_offsets(tile_cnt, rcnt, ntile, a->tile_off, a->pair_base, flag, a->counters, pin.p ? hsz : dsz,
+                              scratch, s));
+  if (!pin.p) MVP_HIP(hipMemcpyAsync(hsz, dsz, sizeof host_sz, hipMemcpyDeviceToHost, s));
   MVP_HIP(hipStreamSynchronize(s));
   pin.synced = true;
   const uint64_t n_tile_pairs = hsz[0], capacity = hsz[1];
@@ -506,8 +492,7 @@ mvp_status build_accel(mvp_ctx *ctx, const mvp_prims *prims, const mvp_camera *c
     MVP_CHECK(ltmp.get(&a->prim_boff, (size_t)kPrimBuckets + 1));
   }
   av = a->view(2);
-  MVP_HIP(launch_zero_u32(tile_cnt, ntile, s));
-  MVP_HIP(launch_tile_fill(av, rect, tile_cnt, a->tile_list, s));
+  MVP_HIP(launch_tile_fill(av, rect, tile_cnt + ntile, a->tile_list, s));
   MVP_HIP(launch_segment_sort(a->tile_off, a->tile_list, (int64_t)ntile, depth, N, tx * ty, s));
   a->item_entries = backward_item_entries(prims->M);
   a->n_items_max = for_backward ? (int64_t)(n_tile_pairs / a->item_entries) + N : 0;
@@ -541,8 +526,6 @@ mvp_status build_accel(mvp_ctx *ctx, const mvp_prims *prims, const mvp_camera *c
   keep.keep = true;
   // temporaries are recycled once the build's kernels have run, except those
   // of the transposed lists, which the structure holds until they are launched
-  // (now, beside the pairs kernel; or after the first forward when that builds
-  // the pairs, so that their launches are off the path to the forward)
   MVP_CHECK(ctx->arena.release_after(temp.list, s));
   temp.keep = true;
   if (for_backward) {
@@ -558,8 +541,6 @@ mvp_status build_accel(mvp_ctx *ctx, const mvp_prims *prims, const mvp_camera *c
   guard.keep = true;
   ctx->live_accels.fetch_add(1);
   *out = a;
-  // beside the pairs kernel; on failure the first backward tries again
-  if (!fuse) (void)launch_lists(a);
   return MVP_OK;
 }
 
@@ -567,7 +548,7 @@ mvp_status destroy_accel(mvp_ctx *ctx, mvp_accel *a, hipStream_t s) {
   if (!ctx || !a || a->ctx != ctx) { set_error("bad accel handle"); return MVP_ERR_INVALID; }
   if (a->lists_pending.exchange(false)) {
     (void)ctx->arena.release_after(a->lists_temps, s);   // never launched: last used by the build
-  } else if (a->lists) {
+  } else if (a->lists_beside) {
     (void)hipStreamWaitEvent(s, a->lists, 0);   // the transposed lists are written on the side stream
   }
   mvp_status st = ctx->arena.release_after(a->blocks, s);
@@ -764,6 +745,17 @@ mvp_status mvp_timing_stop(mvp_ctx *ctx) {
   return MVP_OK;
 }
 
+// Whether counters are still as the build cleared them: once per structure, and
+// never while the stream is captured (a replay has to clear them itself).
+static bool still_clean(std::atomic<bool> &clean, hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    st = hipStreamCaptureStatusActive;
+  }
+  return clean.exchange(false) && st == hipStreamCaptureStatusNone;
+}
+
 // The per-ray pairs, if the build left them to the first forward or backward.
 static mvp_status pairs_ready(const mvp_accel *a, hipStream_t s) {
   if (!a->pairs_pending.exchange(false)) return MVP_OK;
@@ -779,21 +771,21 @@ static mvp_status render_fwd(mvp_ctx *ctx, const mvp_accel *a, const mvp_prims *
   MVP_CHECK(check_render(ctx, a, prims));
   if (!rgba && a->n_slots > 0) { set_error("rgba is NULL"); return MVP_ERR_INVALID; }
   MVP_HIP(hipSetDevice(ctx->device));
-  MVP_HIP(launch_zero_counters(a->counters, 0, kCntFwdPab + 1, s));
+  if (!still_clean(a->fwd_clean, s)) MVP_HIP(launch_zero_counters(a->counters, 0, kCntFwdPab + 1, s));
   MVP_CHECK(pairs_ready(a, s));
   const auto ev = timer_slot(ctx, MVP_KERNEL_FWD_MARCH);
   if (ev.first) MVP_HIP(hipEventRecord(ev.first, s));
   MVP_HIP(launch_march_fwd(a->view(prims->M), *prims, bg, rgba, aux, a->counters, s));
   if (ev.second) MVP_HIP(hipEventRecord(ev.second, s));
-  return launch_lists(a);
+  return aux ? launch_lists(a, s) : MVP_OK;   // (without per-ray state no backward follows)
 }
 
 // What the backward reads of the structure: the pairs (built here if no
 // forward has built them) and the transposed lists (made on the side stream).
 static mvp_status bwd_ready(const mvp_accel *a, hipStream_t s) {
   MVP_CHECK(pairs_ready(a, s));
-  MVP_CHECK(launch_lists(a));
-  if (a->lists) MVP_HIP(hipStreamWaitEvent(s, a->lists, 0));
+  MVP_CHECK(launch_lists(a, s));
+  if (a->lists_beside) MVP_HIP(hipStreamWaitEvent(s, a->lists, 0));
   return MVP_OK;
 }
 
@@ -810,7 +802,8 @@ static mvp_status render_bwd(mvp_ctx *ctx, const mvp_accel *a, const mvp_prims *
   MVP_CHECK(temp.get(&scratch, bwd_scratch_bytes(a->n_rays())));
   const auto ev = timer_slot(ctx, MVP_KERNEL_BWD_MARCH);
   MVP_HIP(launch_march_bwd(a->view(prims->M), *prims, a->n_items_max, aux, grad_rgba, bg, rgba, scratch, grad_payload,
-                           grad_pos, grad_rot, grad_scale, grad_bg, a->counters, s, ev.first, ev.second));
+                           grad_pos, grad_rot, grad_scale, grad_bg, a->counters, still_clean(a->bwd_clean, s), s, ev.first,
+                           ev.second));
   return MVP_OK;   // the scratch is recycled after the kernels have run
 }
 
@@ -849,8 +842,8 @@ mvp_status mvp_render_bwd_noalloc(mvp_ctx *ctx, const mvp_accel *a, const mvp_pr
   MVP_CHECK(bwd_ready(a, (hipStream_t)stream));
   const auto ev = timer_slot(ctx, MVP_KERNEL_BWD_MARCH);
   MVP_HIP(launch_march_bwd(a->view(prims->M), *prims, a->n_items_max, aux, grad_rgba, nullptr, nullptr, ptr,
-                           grad_payload, grad_pos, grad_rot, grad_scale, nullptr, a->counters, (hipStream_t)stream,
-                           ev.first, ev.second));
+                           grad_payload, grad_pos, grad_rot, grad_scale, nullptr, a->counters,
+                           still_clean(a->bwd_clean, (hipStream_t)stream), (hipStream_t)stream, ev.first, ev.second));
   return MVP_OK;
 }
 

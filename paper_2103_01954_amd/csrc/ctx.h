@@ -128,11 +128,15 @@ struct mvp_accel {
   mvp::PairsOut po{};
   mutable std::atomic<bool> pairs_pending{false};
   mutable hipEvent_t pairs_done = nullptr;
-  // The transposed lists are built on the context's side stream, launched
-  // after the first forward (so that their launches are off the path from
-  // the build to the forward) or by the first backward; until then the
+  // The transposed lists are launched after the first forward that leaves state
+  // for a backward (so that their launches are off the path from the build to
+  // the forward) or by the first backward, beside the caller's stream on the
+  // context's side stream or, small ones, on the caller's; until then the
   // structure keeps the temporaries they read.
   mutable std::atomic<bool> lists_pending{false};
+  mutable bool lists_beside = false;   // they are on the side stream, `lists` recorded after them
+  // the counters of the forward and of the backward are as the build cleared them
+  mutable std::atomic<bool> fwd_clean{true}, bwd_clean{true};
   std::vector<void *> lists_temps;
   int4 *rect = nullptr;
   uint32_t *prim_cnt = nullptr;

@@ -66,8 +66,7 @@ struct RayBound {
   float per_sample, clamp;
 };
 
-// Scratch of one backward call over R rays: RayConst [R], RayBound [R] and
-// the payload's largest colour and opacity magnitudes (2 x uint32, float bits).
+// Scratch of one backward call over R rays: RayConst [R] and RayBound [R].
 __host__ __device__ constexpr size_t bwd_scratch_bytes(size_t R) {
   return ((R * sizeof(RayConst) + R * sizeof(RayBound) + 8 + 255) / 256) * 256;
 }
@@ -229,7 +228,8 @@ enum : int {
   kCntPairs = 9,        // build: (ray, primitive) pairs with at least one sample
   kCntSizes = 10,       // build: culling-list entries, pair capacity, ray-subset flags (3 words),
                         // then max |t - o| / min s and max 1 / s over the boxes (float bits, 2 words)
-  kNumCounters = 15
+  kCntPayMax = 15,      // backward: the payload's largest colour and opacity (float bits, 2 x 32 bits)
+  kNumCounters = 16
 };
 constexpr int kCntSlots = 64, kCntStride = 16;   // counter c of copy s at [s * kCntStride + c]
 __device__ __forceinline__ unsigned long long *counter_slot(unsigned long long *counters) {
@@ -246,6 +246,10 @@ hipError_t launch_zero_u32(uint32_t *p, size_t n, hipStream_t s);
 hipError_t launch_zero_u64(uint64_t *p, size_t n, hipStream_t s);
 // clear counters first .. first + n - 1 in every slot
 hipError_t launch_zero_counters(unsigned long long *counters, int first, int n, hipStream_t s);
+// start of a build: clear n_tiles words of tile counters and the counters, and
+// copy the cameras from host_cams (pinned host memory; null: already there)
+hipError_t launch_build_init(uint32_t *tiles, size_t n_tiles, unsigned long long *counters, DevCam *cams,
+                             const DevCam *host_cams, int n_cams, hipStream_t s);
 // exclusive scan of n uint32 counts into n+1 uint64 offsets (scratch from scan_scratch_bytes)
 size_t scan_scratch_bytes(size_t n);
 hipError_t launch_scan_u32_u64(const uint32_t *in, uint64_t *out, size_t n, void *scratch, hipStream_t s);
@@ -256,18 +260,21 @@ hipError_t launch_prep(const mvp_prims &p, const AccelView &av, float4 *xf, int4
                        uint32_t *tile_cnt, unsigned long long *counters, hipStream_t s);
 hipError_t launch_tile_fill(const AccelView &av, const int4 *rect, uint32_t *cursor,
                             uint32_t *tile_list, hipStream_t s);
-// transpose the culling lists (count per primitive, then place each entry
-// from the rectangles), and count the backward work items of every primitive
-hipError_t launch_prim_entry_count(const uint32_t *tile_list, uint64_t n, uint32_t *cnt, hipStream_t s);
-hipError_t launch_prim_entry_place(const AccelView &av, const int4 *rect, uint64_t n, const uint64_t *off,
-                                   uint32_t *prim_entries, hipStream_t s);
-hipError_t launch_item_count(const uint64_t *prim_entry_off, const uint32_t *prim, int n_prim, int per_item,
-                             uint32_t *cnt, hipStream_t s);
-// the backward's order of the primitives (prim[N]) by screen position; key[N],
-// bcnt[kPrimBuckets], boff[kPrimBuckets + 1] and the scan scratch are temporaries
+// offsets of the culling lists (off) and pair slots (base) of every tile from
+// its list length and rays (256, or rays[t] of a ray subset), and the build's
+// five sizes (see write_sizes) to `sizes`, device or pinned host memory
+size_t tile_offsets_scratch_bytes(size_t ntile);
+hipError_t launch_tile_offsets(const uint32_t *cnt, const uint32_t *rays, size_t ntile, uint64_t *off, uint64_t *base,
+                               const uint32_t *flag, const unsigned long long *counters, uint64_t *sizes, void *scratch,
+                               hipStream_t s);
+// the transposed culling lists (primitive -> its entries, from the rectangles)
+// and the backward's work items, with the primitives in screen order (prim[N]);
+// cnt[N + 1], key[N], bcnt[kPrimBuckets], boff[kPrimBuckets + 1] and the scan
+// scratch are temporaries
 constexpr int kPrimBuckets = 4096;
-hipError_t launch_prim_order(const int4 *rect, int N, int V, int tiles_x, int tiles_y, uint32_t *key,
-                             uint32_t *bcnt, uint64_t *boff, void *scan_scratch, uint32_t *prim, hipStream_t s);
+hipError_t launch_prim_lists(const AccelView &av, const int4 *rect, uint64_t n_entries, uint32_t *cnt, uint32_t *key,
+                             uint32_t *bcnt, uint64_t *boff, void *scan_scratch, uint64_t *entry_off, uint32_t *entries,
+                             uint32_t *prim, uint64_t *item_off, hipStream_t s);
 int backward_item_entries(int M);   // culling-list entries per backward work item (<= 64)
 // sort each segment [off[i], off[i+1]) of data (n_seg segments) ascending, or
 // with depth: each tile's culling list by (depth[v N + id], id)
@@ -277,13 +284,6 @@ hipError_t launch_segment_sort(const uint64_t *off, uint32_t *data, int64_t n_se
 // range, 2 = more than 256 rays in a tile), then list them per tile
 hipError_t launch_ray_bin(const AccelView &av, uint32_t *tile_cnt, uint32_t *flag, hipStream_t s);
 hipError_t launch_ray_fill(const AccelView &av, uint32_t *cursor, uint32_t *tile_rays, hipStream_t s);
-// out[0] = *n_entries, out[1] = *capacity, out[2] = *flag (0 if flag is null)
-hipError_t launch_gather_sizes(const uint64_t *n_entries, const uint64_t *capacity, const uint32_t *flag,
-                               uint64_t *out, hipStream_t s);
-// pair capacity of every tile: culling-list length (tile_cnt) times its rays
-// (256, or tile_rays_cnt for a ray subset)
-hipError_t launch_tile_capacity(const uint32_t *tile_cnt, const uint32_t *tile_rays_cnt, size_t ntile, uint32_t *cap,
-                                hipStream_t s);
 // the (ray, primitive) pairs of every ray, the entry frames and the per-entry
 // pair lists (see AccelView); counts the pairs (kCntPairs)
 hipError_t launch_pairs(const AccelView &av, const PairsOut &o, hipStream_t s);
@@ -296,11 +296,12 @@ hipError_t launch_hit_ids(const AccelView &av, const uint64_t *off, int32_t *ids
 hipError_t launch_march_fwd(const AccelView &av, const mvp_prims &p, const float *bg, float *rgba,
                             mvp_ray_aux *aux, unsigned long long *counters, hipStream_t s);
 // backward; scratch holds bwd_scratch_bytes(n_slots) bytes (nothing in it needs
-// to start at zero); bg/rgba/g_bg for a composited forward
+// to start at zero); bg/rgba/g_bg for a composited forward; clean: the counters
+// and kCntPayMax are still as the build cleared them
 hipError_t launch_march_bwd(const AccelView &av, const mvp_prims &p, int64_t n_items_max,
                             const mvp_ray_aux *aux, const float *grad_rgba, const float *bg,
                             const float *rgba, void *scratch, float *g_pay, float *g_pos, float *g_rot,
-                            float *g_scale, float *g_bg, unsigned long long *counters, hipStream_t s,
+                            float *g_scale, float *g_bg, unsigned long long *counters, bool clean, hipStream_t s,
                             hipEvent_t t0 = nullptr,
                             hipEvent_t t1 = nullptr);   // optional events around the per-pair kernel
 

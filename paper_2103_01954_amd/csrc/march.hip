@@ -1847,22 +1847,22 @@ static bool backward_by_runs(const AccelView &av, int M) {
 hipError_t launch_march_bwd(const AccelView &av, const mvp_prims &p, int64_t n_items_max,
                             const mvp_ray_aux *aux, const float *grad_rgba, const float *bg,
                             const float *rgba, void *scratch, float *g_pay, float *g_pos, float *g_rot,
-                            float *g_scale, float *g_bg, unsigned long long *counters, hipStream_t s,
+                            float *g_scale, float *g_bg, unsigned long long *counters, bool clean, hipStream_t s,
                             hipEvent_t t0, hipEvent_t t1) {
   const size_t R = (size_t)av.n_slots;
-  if (counters) {
-    const hipError_t ez = launch_zero_counters(counters, kCntBwdVisit, 4, s);
+  if (!clean) {
+    hipError_t ez = launch_zero_counters(counters, kCntBwdVisit, 4, s);
+    if (ez == hipSuccess) ez = launch_zero_counters(counters, kCntPayMax, 1, s);
     if (ez != hipSuccess) return ez;
   }
   if (R == 0) return hipSuccess;
   RayConst *rc = (RayConst *)scratch;
   RayBound *rbd = (RayBound *)(rc + R);
-  uint32_t *pmax = (uint32_t *)(rbd + R);
+  uint32_t *pmax = (uint32_t *)(counters + kCntPayMax);
   const bool bf16 = p.payload_dtype == MVP_BF16;
   const bool fade = av.fade_alpha > 0.f;
   const size_t fade_shm = fade ? (size_t)p.M * sizeof(float) : 0;
-  hipError_t e = launch_zero_u32(pmax, 2, s);
-  if (e != hipSuccess) return e;
+  hipError_t e = hipSuccess;
   const size_t n_vox = (size_t)p.n_prim * p.M * p.M * p.M;
   if (n_vox) {
     const unsigned pg = (unsigned)std::min<size_t>((n_vox + 255) / 256, 1024);

@@ -247,8 +247,8 @@ void Server::work(Slot &slot) {
                                  /*for_backward=*/false);
     if (st == MVP_OK) {
       slot.accel = a;
-      hipError_t e = launch_zero_counters(a->counters, 0, kCntFwdPab + 1, slot.stream);
-      if (e == hipSuccess && a->pairs_pending.exchange(false)) e = launch_pairs(a->view(prims.M), a->po, slot.stream);
+      hipError_t e = hipSuccess;   // (the build has cleared the counters)
+      if (a->pairs_pending.exchange(false)) e = launch_pairs(a->view(prims.M), a->po, slot.stream);
       if (e == hipSuccess)
         e = launch_march_fwd(a->view(prims.M), prims, nullptr, req.rgba_out, nullptr, a->counters, slot.stream);
       if (e == hipSuccess && slot.h_counts)
