@@ -494,7 +494,7 @@ mvp_status build_accel(mvp_ctx *ctx, const mvp_prims *prims, const mvp_camera *c
   av = a->view(2);
   MVP_HIP(launch_tile_fill(av, rect, tile_cnt + ntile, a->tile_list, s));
   MVP_HIP(launch_segment_sort(a->tile_off, a->tile_list, (int64_t)ntile, depth, N, tx * ty, s));
-  a->item_entries = backward_item_entries(prims->M);
+  a->item_entries = backward_item_entries(prims->M, N, n_tile_pairs);
   a->n_items_max = for_backward ? (int64_t)(n_tile_pairs / a->item_entries) + N : 0;
   // Every ray's pairs, the entry frames and the per-entry pair lists: by the
   // pairs kernel now, with the transposed lists beside it, or, where the march

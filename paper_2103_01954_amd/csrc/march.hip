@@ -1954,11 +1954,24 @@ hipError_t launch_march_bwd(const AccelView &av, const mvp_prims &p, int64_t n_i
   return e;
 }
 
-// Entries per backward work item: 8^3 payloads flush small gradients, so
-// shorter items (more of them) balance better; larger payloads amortise the
-// per-item zeroing and flush of their LDS gradient over 64 entries; those taken
-// in slabs have few primitives and items of at most 4096 pairs, the ordering
-// buffer's size beside a slab.
-int backward_item_entries(int M) { return M <= 8 ? 32 : M <= 16 ? kItemEntries : 16; }
+// Entries per backward work item.  A long item zeroes and flushes its
+// primitive's gradient less often and fills its waves better (rays spread over
+// 4096 tiles, 1 ray each: 786 us with 32 entries, 518 with 64; 32768 of 16^3:
+// 28.3 and 27.4 ms, 35.3 with 16); but where there are few primitives, long
+// items leave workgroups idle at the end (512 of 16^3, 56 entries each, one
+// workgroup per CU: 1953 us with 64 entries, 1625 with 32, 1315 with 16, 1388
+// with 8).  So an item takes 64 entries, or fewer where that is under 8 items
+// for each workgroup that is resident at once; not under 32 for payloads up to
+// 8^3, where it does not pay (4096 of them at 667 x 1024: 690 us with 64 and 32,
+// 699 with 16).  Those taken in slabs have items of at most 4096 pairs, the
+// ordering buffer's size beside a slab (64 of 32^3: 3.6 ms with 16 entries, 4.8
+// with 8 or 32).
+int backward_item_entries(int M, int64_t N, uint64_t n_entries) {
+  if (M > 16) return 16;
+  const uint64_t want = 8 * 256 * (M <= 8 ? 3 : 1);
+  int n = kItemEntries;
+  while (n > (M <= 8 ? 32 : 16) && n_entries / n + (uint64_t)N < want) n /= 2;
+  return n;
+}
 
 }  // namespace mvp
