@@ -908,15 +908,19 @@ hipError_t launch_ray_fill(const AccelView &av, uint32_t *cursor, uint32_t *tile
 // per-ray hit lists
 // ---------------------------------------------------------------------------
 
-__global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(5))) void k_pairs(AccelView av,
+template <bool SUBSET>
+__global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(SUBSET ? 4 : 5))) void k_pairs(AccelView av,
                                                                                                 PairsOut o) {
-  tile_pairs(av, blockIdx.x, o);
+  tile_pairs<SUBSET>(av, blockIdx.x, o);
 }
 
 hipError_t launch_pairs(const AccelView &av, const PairsOut &o, hipStream_t s) {
   const int ntile = av.V * av.tiles_x * av.tiles_y;
   if (ntile == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_pairs, dim3(ntile), dim3(kTileThreads), 0, s, av, o);
+  if (av.tile_rays)
+    hipLaunchKernelGGL((k_pairs<true>), dim3(ntile), dim3(kTileThreads), 0, s, av, o);
+  else
+    hipLaunchKernelGGL((k_pairs<false>), dim3(ntile), dim3(kTileThreads), 0, s, av, o);
   return hipGetLastError();
 }
 
@@ -939,9 +943,9 @@ __global__ __launch_bounds__(kTileThreads) void k_hit_count(AccelView av, uint32
     stage_chunk(sm, av, cam, c0, n);
     __syncthreads();
     for (int e = 0; e < n; ++e) {
-      float a[3], b[3];
-      int jlo, jhi;
-      cnt += (valid && pair_of(sm, e, d, av.t_near, av.step, 1, a, b, &jlo, &jhi)) ? 1u : 0u;
+      float a[3], b[3], t0, t1;
+      local_ray(sm, e, d, a, b);
+      cnt += (valid && slab_test(a, b, av.t_near, &t0, &t1)) ? 1u : 0u;
     }
   }
   if (valid) ray_cnt[slot] = cnt;
@@ -975,9 +979,9 @@ __global__ __launch_bounds__(kTileThreads) void k_hit_ids(AccelView av, const ui
     stage_chunk(sm, av, cam, c0, n);
     __syncthreads();
     for (int e = 0; e < n; ++e) {
-      float a[3], b[3];
-      int jlo, jhi;
-      if (valid && pair_of(sm, e, d, av.t_near, av.step, 1, a, b, &jlo, &jhi)) {
+      float a[3], b[3], t0, t1;
+      local_ray(sm, e, d, a, b);
+      if (valid && slab_test(a, b, av.t_near, &t0, &t1)) {
         const int32_t id = sm.id[e];
         uint64_t at = o++;
         while (at > o0 && ids[at - 1] > id) {
