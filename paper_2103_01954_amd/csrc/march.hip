@@ -921,16 +921,34 @@ __host__ __device__ inline LdsMap lds_map(int M, bool padded) {
   return LdsMap{sy, sz, sz * M};
 }
 
-// One addend of the fixed-point accumulator: v * scale rounded to the nearest
-// integer (|v * scale| < 2^30 by the choice of scale), sign-extended to the
-// 64-bit two's complement word that the LDS atomic adds.
-__device__ __forceinline__ unsigned long long fixed_addend(float v, float scale) {
-  return (unsigned long long)(long long)__float2int_rn(v * scale);
+// One addend of the fixed-point accumulator: v rounded to the nearest integer
+// (|v| < 2^30 by the choice of scale), sign-extended to the 64-bit two's
+// complement word that the LDS atomic adds.  (Rounding down v + 1/2, formed in
+// one fma, saves an instruction but is biased where v has no fraction bits left.)
+__device__ __forceinline__ unsigned long long fixed_addend(float v) {
+  return (unsigned long long)(long long)__float2int_rn(v);
 }
 
+// The scale of a work item's fixed-point gradient as a product of two powers of
+// two of about its root: one goes into the rays' upstream colour gradients, the
+// other into the sums they multiply, so that neither overflows where the
+// product does not and a cell's 32 addends need no scaling of their own.
+struct FixedScale {
+  float g, w, both;
+};
+__device__ __forceinline__ FixedScale split_scale(float scale) {
+  if (!(scale > 0.f)) return FixedScale{0.f, 0.f, 0.f};
+  int e;
+  (void)frexpf(scale, &e);   // scale = 2^(e-1)
+  const int h = (e - 1) / 2;
+  return FixedScale{ldexpf(1.0f, h), ldexpf(1.0f, e - 1 - h), scale};
+}
+
+// Adds a run's corner adjoints: of the colours g times bw, of the opacity b3
+// (LDS_ACC: scaled, see FixedScale).
 template <bool LDS_ACC, bool FADE, typename T>
-__device__ __forceinline__ void flush_cell(T *dst, size_t cell, int M, const LdsMap &lm, const float (&acc)[8][4],
-                                           const float (&wq)[8], unsigned m, float scale) {
+__device__ __forceinline__ void flush_cell(T *dst, size_t cell, int M, const LdsMap &lm, const float (&g)[3],
+                                           const float (&bw)[8], const float (&b3)[8], const float (&wq)[8], unsigned m) {
   // cell: LDS slot of corner (0,0,0) (LDS_ACC) or its voxel index in device memory
   const size_t sy = LDS_ACC ? (size_t)lm.sy : (size_t)M, sz = LDS_ACC ? (size_t)lm.sz : (size_t)M * M;
   const size_t plane = (size_t)lm.plane;
@@ -938,17 +956,14 @@ __device__ __forceinline__ void flush_cell(T *dst, size_t cell, int M, const Lds
   for (int q = 0; q < 8; ++q) {
     const unsigned r = (unsigned)q ^ m;
     const size_t vox = cell + (r & 1u) + ((r >> 1) & 1u) * sy + (r >> 2) * sz;
-    const float a3 = FADE ? acc[q][3] * wq[q] : acc[q][3];
     if constexpr (LDS_ACC) {
-      atomicAdd(dst + vox, fixed_addend(acc[q][0], scale));
-      atomicAdd(dst + plane + vox, fixed_addend(acc[q][1], scale));
-      atomicAdd(dst + 2 * plane + vox, fixed_addend(acc[q][2], scale));
-      atomicAdd(dst + 3 * plane + vox, fixed_addend(a3, scale));
+#pragma unroll
+      for (int c = 0; c < 3; ++c) atomicAdd(dst + c * plane + vox, fixed_addend(g[c] * bw[q]));
+      atomicAdd(dst + 3 * plane + vox, fixed_addend(FADE ? b3[q] * wq[q] : b3[q]));
     } else {
-      unsafeAtomicAdd(dst + vox * 4, acc[q][0]);
-      unsafeAtomicAdd(dst + vox * 4 + 1, acc[q][1]);
-      unsafeAtomicAdd(dst + vox * 4 + 2, acc[q][2]);
-      unsafeAtomicAdd(dst + vox * 4 + 3, a3);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) unsafeAtomicAdd(dst + vox * 4 + c, g[c] * bw[q]);
+      unsafeAtomicAdd(dst + vox * 4 + 3, FADE ? b3[q] * wq[q] : b3[q]);
     }
   }
 }
@@ -1042,7 +1057,7 @@ template <bool BF16, bool LDS_ACC, bool FADE, bool RUNS, bool SLABS, bool PREFET
 __device__ __forceinline__ void bwd_pair(const AccelView &av, const char *__restrict__ payk,
                                          const mvp_ray_aux *__restrict__ aux, const float4 *__restrict__ grad_rgba,
                                          const RayConst *__restrict__ rc, const uint2 rec, uint64_t gent, int tile,
-                                         int k, const float (&t)[3], const Slab &slab, GAcc *gdst, const LdsMap &lm, float fxs,
+                                         int k, const float (&t)[3], const Slab &slab, GAcc *gdst, const LdsMap &lm, const FixedScale &fxs,
                                          const float *s_fade, bool pose,
                                          float (&P)[12], uint32_t &runs) {
   const int M = av.M;
@@ -1067,6 +1082,7 @@ __device__ __forceinline__ void bwd_pair(const AccelView &av, const char *__rest
   int jh = min(jr.y, ax.j_end);
   if (SLABS) clip_to_slab(slab, A.z, B.z, dt, M, hM, jr.x, jh);
   float G0 = 0.f, G1 = 0.f, G2 = 0.f, H0 = 0.f, H1 = 0.f, H2 = 0.f;
+  const float gsc[3] = {g.x * fxs.g, g.y * fxs.g, g.z * fxs.g};
   float4 cv[8];
   float wq[8];
 #pragma unroll
@@ -1254,20 +1270,12 @@ __device__ __forceinline__ void bwd_pair(const AccelView &av, const char *__rest
             for (int q8 = 0; q8 < 8; ++q8)
               if (!(q8 & bit)) o[q8] -= o[q8 | bit];
         };
-        adjoint(bw, W0, W1, W2, W3);
-        adjoint(b3, V0, V1, V2, V3);
-        float acc[8][4];
-  #pragma unroll
-        for (int q8 = 0; q8 < 8; ++q8) {
-          acc[q8][0] = g.x * bw[q8];
-          acc[q8][1] = g.y * bw[q8];
-          acc[q8][2] = g.z * bw[q8];
-          acc[q8][3] = b3[q8];
-        }
+        adjoint(bw, W0 * fxs.w, W1 * fxs.w, W2 * fxs.w, W3 * fxs.w);
+        adjoint(b3, V0 * fxs.both, V1 * fxs.both, V2 * fxs.both, V3 * fxs.both);
         const size_t fc = LDS_ACC ? (size_t)((unsigned)ci0 + __umul24((unsigned)ci1, (unsigned)lm.sy) +
                                              __umul24((unsigned)(SLABS ? ci2 - slab.z0 : ci2), (unsigned)lm.sz))
                                   : (size_t)cell;
-        flush_cell<LDS_ACC, FADE>(gdst, fc, M, lm, acc, wq, m, fxs);
+        flush_cell<LDS_ACC, FADE>(gdst, fc, M, lm, gsc, bw, b3, wq, m);
       }
     }
   } else {
@@ -1337,10 +1345,11 @@ __device__ __forceinline__ void bwd_pair(const AccelView &av, const char *__rest
           ws = dt * sg;
         }
         // adjoint of the monomial coefficients; the corners' are formed at the flush
+        const float wsf = ws * fxs.w, a3f = a3 * fxs.both;
   #pragma unroll
         for (int q = 0; q < 8; ++q) {
-          bw[q] = fmaf(mq[q], ws, bw[q]);
-          b3[q] = fmaf(mq[q], a3, b3[q]);
+          bw[q] = fmaf(mq[q], wsf, bw[q]);
+          b3[q] = fmaf(mq[q], a3f, b3[q]);
         }
         // gradient with respect to the cell offsets of the interpolant of the
         // adjoint-weighted channels: al[q] = a . cf[q], d/dx of sum al[q] m_q
@@ -1373,19 +1382,11 @@ __device__ __forceinline__ void bwd_pair(const AccelView &av, const char *__rest
             bw[q] -= bw[q | bit];
             b3[q] -= b3[q | bit];
           }
-      float acc[8][4];
-  #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        acc[q][0] = g.x * bw[q];
-        acc[q][1] = g.y * bw[q];
-        acc[q][2] = g.z * bw[q];
-        acc[q][3] = b3[q];
-      }
       if (gdst) {
         const size_t fc = LDS_ACC ? (size_t)((unsigned)ci0 + __umul24((unsigned)ci1, (unsigned)lm.sy) +
                                              __umul24((unsigned)(SLABS ? ci2 - slab.z0 : ci2), (unsigned)lm.sz))
                                   : (size_t)cell;
-        flush_cell<LDS_ACC, FADE>(gdst, fc, M, lm, acc, wq, m, fxs);
+        flush_cell<LDS_ACC, FADE>(gdst, fc, M, lm, gsc, bw, b3, wq, m);
       }
     }
   }
@@ -1614,6 +1615,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES))
     for (int i = 0; i < 12; ++i) P[i] = 0.f;
     float bound = 0.f;   // largest bound of this thread's pairs, then of the item's
     float fscale = 1.0f;
+    FixedScale fxs{1.0f, 1.0f, 1.0f};
     if (kSortPairs && total <= sort_cap) {
       // Counting sort of the item's pairs by length class, longest first, in a
       // fixed order (class, then round r = the r-th pair of every thread's
@@ -1651,6 +1653,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES))
 #pragma unroll
       for (int w = 0; w < THREADS / kWave; ++w) bound = nan_max(bound, s_bnd[w]);
       fscale = fixed_scale(bound);
+      fxs = split_scale(fscale);
       if (wave == 0) {   // exclusive scan over the classes from the longest down
         const uint32_t c = s_cls[kLenBuckets - 1 - lane];
         uint32_t incl = c;
@@ -1706,7 +1709,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES))
         }
         const uint2 rec = av.ent_rec[s_start[q] + (i - s_pre[q])];
         bwd_pair<BF16, LDS_ACC, FADE, RUNS, SLABS, WAVES == 1>(av, payk, aux, grad_rgba, rc, rec, s_gent[q >> 2], s_tile[q >> 2], k, t, slab, gdst,
-                                      lm, fscale, s_fade, pose, P, n_run);
+                                      lm, fxs, s_fade, pose, P, n_run);
         ++n_rep;
       }
     } else {
@@ -1741,12 +1744,13 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES))
 #pragma unroll
         for (int w = 0; w < THREADS / kWave; ++w) bound = nan_max(bound, s_bnd[w]);
         fscale = fixed_scale(bound);
+      fxs = split_scale(fscale);
       }
       for (uint32_t i = i0, q = q0; i < iend; i += stride) {
         while (s_pre[q + 1] <= i) ++q;
         const uint2 rec = av.ent_rec[s_start[q] + (i - s_pre[q])];
         bwd_pair<BF16, LDS_ACC, FADE, RUNS, SLABS, WAVES == 1>(av, payk, aux, grad_rgba, rc, rec, s_gent[q >> 2], s_tile[q >> 2], k, t, slab, gdst,
-                                      lm, fscale, s_fade, pose, P, n_run);
+                                      lm, fxs, s_fade, pose, P, n_run);
         ++n_rep;
       }
     }
