@@ -197,7 +197,7 @@ mvp_status mvp_render_fwd(mvp_ctx *ctx, const mvp_accel *accel, const mvp_prims 
  *   grad_payload [N,M,M,M,4] float32 (also for bf16 payloads),
  *   grad_pos [N,3], grad_rot [N,3,3], grad_scale [N,3] float32;
  * any of the four may be NULL to skip it.  A primitive's payload gradient is
- * summed per work item (up to 64 screen tiles of one primitive) in on-chip
+ * summed per work item (up to 128 screen tiles of one primitive) in on-chip
  * memory as 64-bit fixed point, with a scale chosen per item from a bound on
  * what any one of its (ray, primitive) pairs contributes, so that no sum
  * overflows and the integer sums do not depend on the order of the additions;

@@ -494,14 +494,14 @@ mvp_status build_accel(mvp_ctx *ctx, const mvp_prims *prims, const mvp_camera *c
   av = a->view(2);
   MVP_HIP(launch_tile_fill(av, rect, tile_cnt + ntile, a->tile_list, s));
   MVP_HIP(launch_segment_sort(a->tile_off, a->tile_list, (int64_t)ntile, depth, N, tx * ty, s));
-  a->item_entries = backward_item_entries(prims->M, N, n_tile_pairs);
+  a->item_entries = backward_item_entries(av, prims->M, n_tile_pairs, capacity);
   a->n_items_max = for_backward ? (int64_t)(n_tile_pairs / a->item_entries) + N : 0;
   // Every ray's pairs, the entry frames and the per-entry pair lists: by the
   // pairs kernel now, with the transposed lists beside it, or, where the march
   // is long enough to hide those (8192 tiles of payloads of at most 8^3), with
   // the first forward, so that their launches are off the path to it.
   a->po = PairsOut{a->ef, a->pr, a->ray_seg, a->ray_nj, a->ent_base, a->ent_n, a->ent_tile, a->ent_rec,
-                   a->counters};
+                   a->counters, !for_backward || backward_by_runs(av, prims->M)};
   // MVP_PAIRS_IN_FORWARD=1 or 0 overrides the choice (tests and tuning)
   const char *force = getenv("MVP_PAIRS_IN_FORWARD");
   const bool fuse = force && (force[0] == '0' || force[0] == '1') ? force[0] == '1' : prims->M <= 8 && ntile >= 8192;

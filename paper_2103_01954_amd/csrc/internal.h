@@ -118,6 +118,7 @@ struct PairsOut {
   uint32_t *ent_tile;
   uint2 *ent_rec;
   unsigned long long *counters;   // adds to kCntPairs
+  bool square;   // a wave's rays are 8 x 8 pixels of the tile, not 4 rows of it
 };
 
 // Workgroups are dispatched round-robin over the 8 XCDs, each with its own L2:
@@ -275,8 +276,10 @@ constexpr int kPrimBuckets = 4096;
 hipError_t launch_prim_lists(const AccelView &av, const int4 *rect, uint64_t n_entries, uint32_t *cnt, uint32_t *key,
                              uint32_t *bcnt, uint64_t *boff, void *scan_scratch, uint64_t *entry_off, uint32_t *entries,
                              uint32_t *prim, uint64_t *item_off, hipStream_t s);
-// culling-list entries per backward work item (<= 64), for N primitives with n_entries in all
-int backward_item_entries(int M, int64_t N, uint64_t n_entries);
+// Whether the backward takes cell runs in closed form, and its culling-list
+// entries per work item, of n_entries entries with n_slots rays in all.
+bool backward_by_runs(const AccelView &av, int M);
+int backward_item_entries(const AccelView &av, int M, uint64_t n_entries, uint64_t n_slots);
 // sort each segment [off[i], off[i+1]) of data (n_seg segments) ascending, or
 // with depth: each tile's culling list by (depth[v N + id], id)
 hipError_t launch_segment_sort(const uint64_t *off, uint32_t *data, int64_t n_seg, const uint32_t *depth, int N,

@@ -50,10 +50,13 @@
 namespace mvp {
 
 // Largest number of culling-list entries per backward work item (the build
-// picks the number per structure, see backward_item_entries), and how the
+// picks the number per structure, see backward_item_entries), the shape of those
+// of sparse rays (that many entries for a workgroup of 64), and how the
 // pairs of an item too large for the ordering buffer (below) are dealt to its
 // threads.
 constexpr int kItemEntries = 64;
+constexpr int kSparseMaxM = 10;   // largest payload for it
+constexpr int kSparseThreads = kWave, kSparseEntries = 128, kSparseSort = 1024;   // pairs it orders
 constexpr bool kChunkedPairs = true;
 // Lanes accumulate in cell coordinates mirrored by (lane mod 8), so lanes that
 // flush the same cell add to different corners in each instruction.
@@ -382,12 +385,22 @@ __device__ __forceinline__ void corners_at(const char *p, size_t row, size_t sli
 // Blocks of 2 x 2 tiles against 4 x 4: a 256 x 256 picture 0.21 against 0.36 ms
 // (4 x 4 gives each XCD two blocks), 32768 x 16^3 12.6 against 14.5 ms, one
 // 1024^2 view of 4096 x 8^3 1.90 against 1.80 ms.
+//
+// A ray subset's units (8 rays each, in the order of their tiles) go to the XCDs
+// in runs of kSubsetRun, likewise dealt in turn: 131072 rays over 16384 tiles of
+// 4096 x 8^3 616 against 644 us with neighbours on different XCDs, 16384 rays 412
+// against 424.
+constexpr int kSubsetRun = 16;
 constexpr int kMarchBlock = 2;
 constexpr int kUnitW = 4, kUnitH = 2;   // pixels of a unit
 constexpr int kUnitsPerTile = kTileThreads / kRaysPerWave;
 constexpr int kUnitsPerBlock = kMarchBlock * kMarchBlock * kUnitsPerTile;
 
 __host__ __device__ __forceinline__ int64_t march_units(const AccelView &av) {
+  if (av.tile_rays) {   // whole runs for every XCD
+    constexpr int64_t turn = kXcd * kSubsetRun * kRaysPerWave;
+    return (av.n_slots + turn - 1) / turn * (kXcd * kSubsetRun);
+  }
   const int64_t bx = (av.tiles_x + kMarchBlock - 1) / kMarchBlock, by = (av.tiles_y + kMarchBlock - 1) / kMarchBlock;
   const int64_t blocks = bx * by * av.V;
   return (blocks + kXcd - 1) / kXcd * kXcd * kUnitsPerBlock;
@@ -436,7 +449,8 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
     int tile = 0, v = 0, px = 0, py = 0;
     bool valid;
     if (av.tile_rays) {   // ray subset: consecutive entries of the tiles' ray lists
-      const int64_t p = u * kRaysPerWave + rl;
+      const int64_t i = u / kXcd, m = i / kSubsetRun;
+      const int64_t p = ((m * kXcd + ((u + 3 * m) & (kXcd - 1))) * kSubsetRun + i % kSubsetRun) * kRaysPerWave + rl;
       valid = p < av.n_slots;
       if (valid) {
         ray = av.tile_rays[p];
@@ -688,7 +702,7 @@ hipError_t launch_march_fwd(const AccelView &av, const mvp_prims &p, const float
                             mvp_ray_aux *aux, unsigned long long *counters, hipStream_t s) {
   const int64_t ntile = (int64_t)av.V * av.tiles_x * av.tiles_y;
   if (ntile == 0 || av.n_slots == 0) return hipSuccess;
-  const int64_t units = av.tile_rays ? (av.n_slots + kRaysPerWave - 1) / kRaysPerWave : march_units(av);
+  const int64_t units = march_units(av);
   const int grid = (int)std::min<int64_t>((units + kXcd - 1) / kXcd * kXcd, 1 << 22);   // a multiple of kXcd
   const bool fade = av.fade_alpha > 0.f;
   const size_t shm = fade ? (size_t)av.M * sizeof(float) : 0;
@@ -1476,7 +1490,7 @@ __device__ __forceinline__ int pair_len(const AccelView &av, const mvp_ray_aux *
 // to any one gradient value.  A cell run adds part of one pair's share, so
 // with the scale below every addend is under 2^29 (half of that covers the
 // rounding of the run's sums) and fits 32 bits; an item has at most
-// 64 entries x 256 rays = 2^14 pairs, so a 64-bit sum stays under 2^43.
+// 128 entries x 256 rays = 2^15 pairs, so a 64-bit sum stays under 2^44.
 // 0 for a non-finite bound (the item's gradient is then written as NaN).
 __device__ __forceinline__ float fixed_scale(float bound) {
   if (!(bound < INFINITY)) return 0.0f;
@@ -1522,12 +1536,14 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES))
   __shared__ float s_bnd[THREADS / kWave];
   // the pairs of an item come in sub-lists, four per entry (the rays of each
   // wave of its tile): their starts in ent_rec and their prefix sums
-  constexpr int kSub = 4 * kItemEntries;
+  constexpr int kEnt = THREADS == kSparseThreads ? kSparseEntries : kItemEntries;
+  constexpr int kSub = 4 * kEnt;
+  constexpr int kSubRounds = (kSub + THREADS - 1) / THREADS;
   __shared__ uint64_t s_start[kSub];
   __shared__ uint32_t s_pre[kSub + 1];
   __shared__ uint32_t s_wsum[kSub / kWave];
-  __shared__ uint64_t s_gent[kItemEntries];
-  __shared__ int s_tile[kItemEntries];
+  __shared__ uint64_t s_gent[kEnt];
+  __shared__ int s_tile[kEnt];
   __shared__ int s_prim, s_pos;
   const int M = av.M;
   const size_t M3 = (size_t)M * M * M;
@@ -1571,9 +1587,12 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES))
     const uint64_t eb = av.prim_entry_off[k] + chunk * (uint64_t)av.item_entries;
     const int nent = (int)min<uint64_t>((uint64_t)av.item_entries, av.prim_entry_off[k + 1] - eb);
     const int nsub = 4 * nent;
-    uint32_t incl = 0;
-    if (threadIdx.x < kSub) {   // sub-list u = 4 q + w: entry q, wave w of its tile
-      const int u = threadIdx.x, q = u >> 2, w = u & 3;
+    uint32_t incl[kSubRounds];
+#pragma unroll
+    for (int r = 0; r < kSubRounds; ++r) {
+      const int u = r * THREADS + (int)threadIdx.x;   // sub-list u = 4 q + w: entry q, wave w of its tile
+      if (u >= kSub) break;                           // (whole waves)
+      const int q = u >> 2, w = u & 3;
       uint32_t cnt = 0;
       if (u < nsub) {
         const uint32_t g = av.prim_entries[eb + q];
@@ -1584,23 +1603,26 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES))
           s_tile[q] = (int)av.ent_tile[g];
         }
       }
-      incl = cnt;
 #pragma unroll
       for (int d = 1; d < kWave; d <<= 1) {
-        const uint32_t o = __shfl_up(incl, d, kWave);
-        if (lane >= d) incl += o;
+        const uint32_t o = __shfl_up(cnt, d, kWave);
+        if (lane >= d) cnt += o;
       }
-      if (lane == kWave - 1) s_wsum[wave] = incl;
+      incl[r] = cnt;
+      if (lane == kWave - 1) s_wsum[u / kWave] = cnt;
     }
     if (LDS_ACC && out.pay)
       for (int i = threadIdx.x; i < nlds; i += THREADS) s_grad[i] = (GAcc)0;
     __syncthreads();
-    if (threadIdx.x < kSub) {   // prefix sums over the sub-lists
+#pragma unroll
+    for (int r = 0; r < kSubRounds; ++r) {   // prefix sums over the sub-lists
+      const int u = r * THREADS + (int)threadIdx.x;
+      if (u >= kSub) break;
       uint32_t base = 0;
 #pragma unroll
-      for (int w = 0; w < kSub / kWave; ++w) base += w < wave ? s_wsum[w] : 0u;
-      if (threadIdx.x == 0) s_pre[0] = 0;
-      s_pre[threadIdx.x + 1] = base + incl;
+      for (int w = 0; w < kSub / kWave; ++w) base += w < u / kWave ? s_wsum[w] : 0u;
+      if (u == 0) s_pre[0] = 0;
+      s_pre[u + 1] = base + incl[r];
     }
     __syncthreads();
     const uint32_t total = s_pre[nsub];
@@ -1653,7 +1675,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES))
 #pragma unroll
       for (int w = 0; w < THREADS / kWave; ++w) bound = nan_max(bound, s_bnd[w]);
       fscale = fixed_scale(bound);
-      fxs = split_scale(fscale);
+      if (LDS_ACC) fxs = split_scale(fscale);
       if (wave == 0) {   // exclusive scan over the classes from the longest down
         const uint32_t c = s_cls[kLenBuckets - 1 - lane];
         uint32_t incl = c;
@@ -1744,7 +1766,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES))
 #pragma unroll
         for (int w = 0; w < THREADS / kWave; ++w) bound = nan_max(bound, s_bnd[w]);
         fscale = fixed_scale(bound);
-      fxs = split_scale(fscale);
+      if (LDS_ACC) fxs = split_scale(fscale);
       }
       for (uint32_t i = i0, q = q0; i < iend; i += stride) {
         while (s_pre[q + 1] <= i) ++q;
@@ -1809,13 +1831,16 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES))
 }
 
 // The work-item kernel for 3 waves per SIMD, 2 workgroups per CU, one of 512
-// threads, or one of 512 threads in slabs.
-enum class BwdShape { kThree, kTwo, kOne, kSlabs };
+// threads, one of 512 threads in slabs, or of 64 threads for sparse rays.
+enum class BwdShape { kThree, kTwo, kOne, kSlabs, kSparse };
 typedef void (*BwdItemsFn)(AccelView, const float *, const float *, const void *, const mvp_ray_aux *, const float4 *,
                            const RayConst *, const RayBound *, BwdOut, uint32_t, int, int, unsigned long long *);
 template <bool B, bool L, bool F, bool R>
 static BwdItemsFn bwd_items_fn(BwdShape shape) {
   if (shape == BwdShape::kThree) return k_bwd_items<B, L, F, R, 3, kTileThreads>;
+  if constexpr (R) {
+    if (shape == BwdShape::kSparse) return k_bwd_items<B, L, F, true, 1, kSparseThreads>;
+  }
   if constexpr (L) {
     if (shape == BwdShape::kSlabs) return k_bwd_items<B, L, F, R, 1, 2 * kTileThreads, true>;
     if (shape == BwdShape::kOne) return k_bwd_items<B, L, F, R, 1, 2 * kTileThreads>;
@@ -1843,7 +1868,7 @@ static BwdItemsFn bwd_items_fn(bool bf16, bool lds, bool fade, bool runs, BwdSha
 //   210); the closed form has less of it (1e-6), but past this line the change
 //   from the one to the other would be larger than a gradient may move between
 //   versions (2e-5).
-static bool backward_by_runs(const AccelView &av, int M) {
+bool backward_by_runs(const AccelView &av, int M) {
   const float cell = 2.0f / (av.max_inv_scale * (float)(M - 1));
   return cell >= 3.0f * av.step && av.max_dist_ratio <= 90.0f;
 }
@@ -1918,7 +1943,8 @@ hipError_t launch_march_bwd(const AccelView &av, const mvp_prims &p, int64_t n_i
   // 3 waves per SIMD when 3 workgroups' LDS fits a CU; 512-thread workgroups
   // when only one does (16^3 payloads: 131 KB)
   const int wgs_fit = in_lds ? wgs_per_cu(lds) : 3;
-  BwdShape shape = slab_cells ? BwdShape::kSlabs : wgs_fit >= 3 ? BwdShape::kThree : wgs_fit == 2 ? BwdShape::kTwo : BwdShape::kOne;
+  const bool sparse = av.item_entries > kItemEntries;
+  BwdShape shape = sparse ? BwdShape::kSparse : slab_cells ? BwdShape::kSlabs : wgs_fit >= 3 ? BwdShape::kThree : wgs_fit == 2 ? BwdShape::kTwo : BwdShape::kOne;
   auto wide = [&] { return shape == BwdShape::kOne || shape == BwdShape::kSlabs; };
   const int64_t n_slab = slab_cells ? (p.M - 2 + slab_cells) / slab_cells : 1;
   const unsigned grid = (unsigned)std::min<int64_t>(n_items_max * n_slab, 1 << 20);
@@ -1932,7 +1958,7 @@ hipError_t launch_march_bwd(const AccelView &av, const mvp_prims &p, int64_t n_i
     const size_t wgs = shape == BwdShape::kThree ? 3 : (shm + kStatic <= 80 * 1024 ? 2 : 1);
     const size_t share = 160 * 1024 / wgs - (wide() ? 2 * kStatic : kStatic);
     const size_t room = share > shm ? (share - shm) / (sizeof(uint16_t) + 1) : 0;
-    const size_t want = (size_t)av.item_entries * kTileThreads;
+    const size_t want = sparse ? kSparseSort : (size_t)av.item_entries * kTileThreads;
     sort_cap = (uint32_t)(std::min(room, want) / kTileThreads * kTileThreads);
     shm += (size_t)sort_cap * (sizeof(uint16_t) + 1);
   }
@@ -1943,7 +1969,7 @@ hipError_t launch_march_bwd(const AccelView &av, const mvp_prims &p, int64_t n_i
     if (hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) != hipSuccess) {
       (void)hipGetLastError();
       // gradients straight to device memory, pairs in list order
-      shape = BwdShape::kThree;
+      shape = sparse ? BwdShape::kSparse : BwdShape::kThree;
       slab_cells = 0;
       sort_cap = 0;
       shm = fade_shm;
@@ -1951,30 +1977,45 @@ hipError_t launch_march_bwd(const AccelView &av, const mvp_prims &p, int64_t n_i
     }
   }
   if (t0) (void)hipEventRecord(t0, s);
-  hipLaunchKernelGGL(fn, dim3(grid), dim3(wide() ? 2 * kTileThreads : kTileThreads), shm, s, av, p.rot, p.scale, p.payload,
+  hipLaunchKernelGGL(fn, dim3(grid), dim3(sparse ? kSparseThreads : wide() ? 2 * kTileThreads : kTileThreads), shm, s, av, p.rot, p.scale, p.payload,
                      aux, (const float4 *)grad_rgba, rc, rbd, out, sort_cap, padded, slab_cells, counters);
   e = hipGetLastError();
   if (t1) (void)hipEventRecord(t1, s);
   return e;
 }
 
-// Entries per backward work item.  A long item zeroes and flushes its
-// primitive's gradient less often and fills its waves better (rays spread over
-// 4096 tiles, 1 ray each: 786 us with 32 entries, 518 with 64; 32768 of 16^3:
-// 28.3 and 27.4 ms, 35.3 with 16); but where there are few primitives, long
-// items leave workgroups idle at the end (512 of 16^3, 56 entries each, one
-// workgroup per CU: 1953 us with 64 entries, 1625 with 32, 1315 with 16, 1388
-// with 8).  So an item takes 64 entries, or fewer where that is under 8 items
-// for each workgroup that is resident at once; not under 32 for payloads up to
-// 8^3, where it does not pay (4096 of them at 667 x 1024: 690 us with 64 and 32,
-// 699 with 16).  Those taken in slabs have items of at most 4096 pairs, the
-// ordering buffer's size beside a slab (64 of 32^3: 3.6 ms with 16 entries, 4.8
-// with 8 or 32).
-int backward_item_entries(int M, int64_t N, uint64_t n_entries) {
+// Entries per backward work item.
+//
+// Closed-form runs: a long item zeroes and flushes its primitive's gradient
+// less often and fills its waves better (rays spread over 4096 tiles, 1 ray
+// each: 786 us with 32 entries, 518 with 64); but where there are few
+// primitives, long items leave workgroups idle at the end (512 of 16^3, 56
+// entries each, one workgroup per CU: 1953 us with 64 entries, 1625 with 32, 1315
+// with 16, 1388 with 8).  So an item takes 64 entries, or fewer where that is
+// under 8 items for each workgroup that is resident at once; not under 32 for
+// payloads up to 8^3, where it does not pay (4096 of them at 667 x 1024: 690 us
+// with 64 and 32, 699 with 16).
+//
+// Sparse rays (n_slots, the rays of all entries' tiles, few per entry) leave
+// most of 256 threads without a pair: 128 entries for 64 threads, of which
+// more workgroups fit a CU, up to 8 rays per entry (4096 x 8^3: 1 ray 247 against
+// 518 us, 4 rays 363 against 563, 6 rays 448 against 577, 8 rays 603 and 597), to
+// 10^3 with fewer workgroups per CU up to 5 (1 ray 411 against 610, 4 rays 581
+// against 663, 6 rays 708 against 679); larger ones leave room for three or less.
+//
+// The sample loop keeps items of fixed length, 32 entries to 8^3 and 64 to 16^3:
+// the rounding of its pose sums depends on how they are grouped (see
+// backward_by_runs), and the largest case is fastest at 64 (32768 of 16^3: 28.3
+// ms with 32, 27.4 with 64).  Payloads taken in slabs have items of at most 4096
+// pairs, the ordering buffer's size beside a slab (64 of 32^3: 3.6 ms with 16
+// entries, 4.8 with 8 or 32).
+int backward_item_entries(const AccelView &av, int M, uint64_t n_entries, uint64_t n_slots) {
   if (M > 16) return 16;
+  if (!backward_by_runs(av, M)) return M <= 8 ? 32 : kItemEntries;
+  if (M <= kSparseMaxM && n_slots < (M <= 8 ? 8 : 5) * n_entries) return kSparseEntries;
   const uint64_t want = 8 * 256 * (M <= 8 ? 3 : 1);
   int n = kItemEntries;
-  while (n > (M <= 8 ? 32 : 16) && n_entries / n + (uint64_t)N < want) n /= 2;
+  while (n > (M <= 8 ? 32 : 16) && n_entries / n + (uint64_t)av.N < want) n /= 2;
   return n;
 }
 

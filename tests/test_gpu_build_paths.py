@@ -122,3 +122,38 @@ def test_builds(mvp_ctx, name):
     _gradients_close(acc.render_bwd(dp, aux, full_grad), sub.render_bwd(dp, sub_aux, grad))
     acc.destroy()
     sub.destroy()
+
+
+# payload size, rays in each tile, rays in every 50th tile, dtype, fade: work items of
+# sparse rays take 128 entries and 64 threads; 1024 pairs of one are ordered
+@pytest.mark.parametrize("m,per_tile,crowd,bf16,fade", [(2, 1, 1, False, 0.0), (8, 1, 1, False, 0.0), (8, 6, 6, True, 0.0),
+                                                        (10, 2, 200, False, 6.0), (8, 3, 250, True, 0.0),
+                                                        (11, 1, 1, False, 0.0), (8, 9, 9, False, 0.0)])
+def test_sparse_rays_backward(mvp_ctx, m, per_tile, crowd, bf16, fade):
+    prims = scenes.random_box_scene(431, n=3, m=m, s_lo=1.0, s_hi=1.4, bf16=bf16)
+    prims.payload[..., 3] *= np.float32(0.2)
+    width, height = 400, 300
+    cam = scenes.look_at_camera(np.random.default_rng(432), width, height)
+    params = scenes.MarchParams(1.0 / 64, 1e-6, fade_alpha=fade, fade_beta=8.0 if fade else 0.0)
+    rng = np.random.default_rng(433)
+    pix = np.arange(width * height)
+    tile = (pix // width // 16) * 25 + (pix % width) // 16
+    ids = np.concatenate([rng.permutation(pix[tile == k])[:crowd if k % 50 == 0 else per_tile] for k in range(25 * 19)])
+    ids = torch.from_numpy(ids.astype(np.int64)).cuda()
+    dp = DevicePrims.from_host(prims)
+    full = mvp_ctx.build_accel(dp, [cam], params)
+    sub = mvp_ctx.build_accel(dp, [cam], params, rays=ids)
+    want, aux = full.render_fwd(dp)
+    got, sub_aux = sub.render_fwd(dp)
+    assert torch.equal(got, want.reshape(-1, 4)[ids])
+    grad = torch.randn(got.shape, generator=torch.Generator("cuda").manual_seed(434), device="cuda")
+    full_grad = torch.zeros_like(want)
+    full_grad.reshape(-1, 4)[ids] = grad
+    _gradients_close(sub.render_bwd(dp, sub_aux, grad), full.render_bwd(dp, aux, full_grad))
+    pose_only = {k: torch.zeros_like(getattr(dp, k)) for k in ("pos", "rot", "scale")}
+    with_payload = sub.render_bwd(dp, sub_aux, grad)
+    sub.render_bwd(dp, sub_aux, grad, pose_only)
+    for k, v in pose_only.items():
+        assert float((v - with_payload[k]).abs().max()) <= 5e-5 * float(v.abs().max()), k
+    full.destroy()
+    sub.destroy()
