@@ -290,10 +290,10 @@ __device__ bool seq_sample(const AccelView &av, uint64_t lb, const void *pay, co
 // BF16 ones.  8 samples rather than 16: a window of 16 leaves 6% more lanes
 // idle at the ends of the pairs and takes more pairs per window.
 // Measured (march and pairs kernels together, one ray per lane -> this):
-// 512 x 16^3 BF16 at 256^2 1.40 -> 0.31 ms, 4096 x 8^3 FP32 at 1024^2
-// 4.15 -> 2.20 ms and four such views 8.0 -> 8.1 ms, 2048 x 12^3 BF16 at
-// 1920 x 1080 5.8 -> 4.2 ms, 32768 x 16^3 BF16 at 2 x 2048^2 21.0 -> 14.1 ms,
-// 16384 sampled rays of four 1024^2 views 2.6 -> 0.45 ms.
+// 512 x 16^3 BF16 at 256^2 1.40 -> 0.26 ms, 4096 x 8^3 FP32 at 1024^2
+// 4.15 -> 2.05 ms and four such views 8.0 -> 7.75 ms, 2048 x 12^3 BF16 at
+// 1920 x 1080 5.8 -> 4.15 ms, 32768 x 16^3 BF16 at 2 x 2048^2 21.0 -> 13.8 ms,
+// 16384 sampled rays of four 1024^2 views 2.6 -> 0.53 ms.
 constexpr int kWin = 8;
 constexpr int kRaysPerWave = kWave / kWin;
 // Pairs staged per ray in LDS: a ring, refilled kBatch at a time (each lane
