@@ -939,7 +939,20 @@ __host__ __device__ inline LdsMap lds_map(int M, bool padded) {
 // (|v| < 2^30 by the choice of scale), sign-extended to the 64-bit two's
 // complement word that the LDS atomic adds.  (Rounding down v + 1/2, formed in
 // one fma, saves an instruction but is biased where v has no fraction bits left.)
+//
+// WIDE (payloads taken in slabs, sparse rays): |v| < 2^44, converted in two
+// exact parts.  The scale follows the largest bound of an item's pairs, which
+// may be thousands of times what most voxels get (a ray that saturates in a
+// faint sample): with 30 bits the rounding of every addend then shows in the
+// gradient (970 x 24^3 with the fade window: over 1e-6 of it), with 44 bits only
+// the FP32 rounding of the run's own sums is left.
+template <bool WIDE>
 __device__ __forceinline__ unsigned long long fixed_addend(float v) {
+  if constexpr (WIDE) {
+    const float h = rintf(v * 0x1p-20f);
+    const float l = fmaf(h, -0x1p20f, v);
+    return (unsigned long long)((long long)(int)h * (1ll << 20) + (long long)__float2int_rn(l));
+  }
   return (unsigned long long)(long long)__float2int_rn(v);
 }
 
@@ -960,7 +973,7 @@ __device__ __forceinline__ FixedScale split_scale(float scale) {
 
 // Adds a run's corner adjoints: of the colours g times bw, of the opacity b3
 // (LDS_ACC: scaled, see FixedScale).
-template <bool LDS_ACC, bool FADE, typename T>
+template <bool LDS_ACC, bool FADE, bool WIDE, typename T>
 __device__ __forceinline__ void flush_cell(T *dst, size_t cell, int M, const LdsMap &lm, const float (&g)[3],
                                            const float (&bw)[8], const float (&b3)[8], const float (&wq)[8], unsigned m) {
   // cell: LDS slot of corner (0,0,0) (LDS_ACC) or its voxel index in device memory
@@ -972,8 +985,8 @@ __device__ __forceinline__ void flush_cell(T *dst, size_t cell, int M, const Lds
     const size_t vox = cell + (r & 1u) + ((r >> 1) & 1u) * sy + (r >> 2) * sz;
     if constexpr (LDS_ACC) {
 #pragma unroll
-      for (int c = 0; c < 3; ++c) atomicAdd(dst + c * plane + vox, fixed_addend(g[c] * bw[q]));
-      atomicAdd(dst + 3 * plane + vox, fixed_addend(FADE ? b3[q] * wq[q] : b3[q]));
+      for (int c = 0; c < 3; ++c) atomicAdd(dst + c * plane + vox, fixed_addend<WIDE>(g[c] * bw[q]));
+      atomicAdd(dst + 3 * plane + vox, fixed_addend<WIDE>(FADE ? b3[q] * wq[q] : b3[q]));
     } else {
 #pragma unroll
       for (int c = 0; c < 3; ++c) unsafeAtomicAdd(dst + vox * 4 + c, g[c] * bw[q]);
@@ -1067,7 +1080,7 @@ __device__ __forceinline__ void clip_to_slab(const Slab &sl, float a, float b, f
 // 8^3, four 1024^2 views (5 samples per run): 6.5 -> 4.2 ms; 512 x 16^3 at
 // 667 x 1024: 4.4 -> 1.9 ms.  At 2 samples per run the two are equal (32768 x
 // 16^3 at 2 x 2048^2: 26.8 and 27.0 ms): see backward_by_runs.
-template <bool BF16, bool LDS_ACC, bool FADE, bool RUNS, bool SLABS, bool PREFETCH, typename GAcc>
+template <bool BF16, bool LDS_ACC, bool FADE, bool RUNS, bool SLABS, bool PREFETCH, bool WIDE, typename GAcc>
 __device__ __forceinline__ void bwd_pair(const AccelView &av, const char *__restrict__ payk,
                                          const mvp_ray_aux *__restrict__ aux, const float4 *__restrict__ grad_rgba,
                                          const RayConst *__restrict__ rc, const uint2 rec, uint64_t gent, int tile,
@@ -1289,7 +1302,7 @@ __device__ __forceinline__ void bwd_pair(const AccelView &av, const char *__rest
         const size_t fc = LDS_ACC ? (size_t)((unsigned)ci0 + __umul24((unsigned)ci1, (unsigned)lm.sy) +
                                              __umul24((unsigned)(SLABS ? ci2 - slab.z0 : ci2), (unsigned)lm.sz))
                                   : (size_t)cell;
-        flush_cell<LDS_ACC, FADE>(gdst, fc, M, lm, gsc, bw, b3, wq, m);
+        flush_cell<LDS_ACC, FADE, WIDE>(gdst, fc, M, lm, gsc, bw, b3, wq, m);
       }
     }
   } else {
@@ -1400,7 +1413,7 @@ __device__ __forceinline__ void bwd_pair(const AccelView &av, const char *__rest
         const size_t fc = LDS_ACC ? (size_t)((unsigned)ci0 + __umul24((unsigned)ci1, (unsigned)lm.sy) +
                                              __umul24((unsigned)(SLABS ? ci2 - slab.z0 : ci2), (unsigned)lm.sz))
                                   : (size_t)cell;
-        flush_cell<LDS_ACC, FADE>(gdst, fc, M, lm, gsc, bw, b3, wq, m);
+        flush_cell<LDS_ACC, FADE, WIDE>(gdst, fc, M, lm, gsc, bw, b3, wq, m);
       }
     }
   }
@@ -1490,14 +1503,16 @@ __device__ __forceinline__ int pair_len(const AccelView &av, const mvp_ray_aux *
 // to any one gradient value.  A cell run adds part of one pair's share, so
 // with the scale below every addend is under 2^29 (half of that covers the
 // rounding of the run's sums) and fits 32 bits; an item has at most
-// 128 entries x 256 rays = 2^15 pairs, so a 64-bit sum stays under 2^44.
+// 128 entries x 256 rays = 2^15 pairs, so a 64-bit sum stays under 2^44 (WIDE:
+// addends under 2^43, sums under 2^58).
 // 0 for a non-finite bound (the item's gradient is then written as NaN).
+template <bool WIDE>
 __device__ __forceinline__ float fixed_scale(float bound) {
   if (!(bound < INFINITY)) return 0.0f;
   if (!(bound > 0.0f)) return 1.0f;
   int e;
   (void)frexpf(2.0f * bound, &e);   // 2 bound = m 2^e, 0.5 <= m < 1, so bound < 2^(e-1)
-  return ldexpf(1.0f, min(max(30 - e, -126), 126));
+  return ldexpf(1.0f, min(max((WIDE ? 44 : 30) - e, -126), 126));
 }
 
 // Length classes for ordering pairs: exact below 32 samples, then 4 wide.
@@ -1536,6 +1551,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES))
   __shared__ float s_bnd[THREADS / kWave];
   // the pairs of an item come in sub-lists, four per entry (the rays of each
   // wave of its tile): their starts in ent_rec and their prefix sums
+  constexpr bool kWide = SLABS || THREADS == kSparseThreads;
   constexpr int kEnt = THREADS == kSparseThreads ? kSparseEntries : kItemEntries;
   constexpr int kSub = 4 * kEnt;
   constexpr int kSubRounds = (kSub + THREADS - 1) / THREADS;
@@ -1674,7 +1690,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES))
       bound = 0.f;
 #pragma unroll
       for (int w = 0; w < THREADS / kWave; ++w) bound = nan_max(bound, s_bnd[w]);
-      fscale = fixed_scale(bound);
+      fscale = fixed_scale<kWide>(bound);
       if (LDS_ACC) fxs = split_scale(fscale);
       if (wave == 0) {   // exclusive scan over the classes from the longest down
         const uint32_t c = s_cls[kLenBuckets - 1 - lane];
@@ -1730,7 +1746,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES))
           if (s_pre[mid] <= i) q = mid; else hi = mid - 1;
         }
         const uint2 rec = av.ent_rec[s_start[q] + (i - s_pre[q])];
-        bwd_pair<BF16, LDS_ACC, FADE, RUNS, SLABS, WAVES == 1>(av, payk, aux, grad_rgba, rc, rec, s_gent[q >> 2], s_tile[q >> 2], k, t, slab, gdst,
+        bwd_pair<BF16, LDS_ACC, FADE, RUNS, SLABS, WAVES == 1, kWide>(av, payk, aux, grad_rgba, rc, rec, s_gent[q >> 2], s_tile[q >> 2], k, t, slab, gdst,
                                       lm, fxs, s_fade, pose, P, n_run);
         ++n_rep;
       }
@@ -1765,13 +1781,13 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES))
         bound = 0.f;
 #pragma unroll
         for (int w = 0; w < THREADS / kWave; ++w) bound = nan_max(bound, s_bnd[w]);
-        fscale = fixed_scale(bound);
+        fscale = fixed_scale<kWide>(bound);
       if (LDS_ACC) fxs = split_scale(fscale);
       }
       for (uint32_t i = i0, q = q0; i < iend; i += stride) {
         while (s_pre[q + 1] <= i) ++q;
         const uint2 rec = av.ent_rec[s_start[q] + (i - s_pre[q])];
-        bwd_pair<BF16, LDS_ACC, FADE, RUNS, SLABS, WAVES == 1>(av, payk, aux, grad_rgba, rc, rec, s_gent[q >> 2], s_tile[q >> 2], k, t, slab, gdst,
+        bwd_pair<BF16, LDS_ACC, FADE, RUNS, SLABS, WAVES == 1, kWide>(av, payk, aux, grad_rgba, rc, rec, s_gent[q >> 2], s_tile[q >> 2], k, t, slab, gdst,
                                       lm, fxs, s_fade, pose, P, n_run);
         ++n_rep;
       }
