@@ -97,6 +97,20 @@ struct Cell {
   float f[3];
 };
 
+// Index of voxel (q0, q1, q2), whole numbers below M <= 1024 held as floats.  A
+// float holds every step exactly up to M = 256; above (BIG) only the inner
+// multiply-add (below 2^20) is, and the index, which reaches 2^30, is formed in
+// integers: one conversion more, 0.9% of a march that is bound by the VALU (2048 x
+// 12^3 BF16 at 1920 x 1080), so the small ones keep the floats.
+constexpr int kFloatIndexM = 256;
+template <bool BIG>
+__device__ __forceinline__ int voxel_index(float q0, float q1, float q2, int M, float Mf) {
+  const float zy = fmaf(q2, Mf, q1);
+  if (BIG) return (int)(__umul24((unsigned)zy, (unsigned)M) + (unsigned)q0);
+  return (int)fmaf(zy, Mf, q0);
+}
+
+template <bool BIG>
 __device__ __forceinline__ Cell locate(const float4 &A, const float4 &B, float tau, int M, float hM) {
   const float y[3] = {fmaf(tau, B.x, A.x), fmaf(tau, B.y, A.y), fmaf(tau, B.z, A.z)};
   const float top = (float)(M - 2), Mf = (float)M;
@@ -112,10 +126,7 @@ __device__ __forceinline__ Cell locate(const float4 &A, const float4 &B, float t
     c.i[i] = (int)qf[i];
     c.f[i] = u - qf[i];
   }
-  // the index from the float coordinates: every term is an integer below 2^24
-  // (M <= 1024), so the two fused multiply-adds are exact, and they are full
-  // rate where a 32-bit integer multiply-add is not
-  c.idx = (int)fmaf(fmaf(qf[2], Mf, qf[1]), Mf, qf[0]);
+  c.idx = voxel_index<BIG>(qf[0], qf[1], qf[2], M, Mf);
   return c;
 }
 
@@ -202,7 +213,7 @@ __device__ __forceinline__ float4 sample_pair(const AccelView &av, const void *p
                                               const float4 &B, float tau) {
   const int M = av.M;
   const float hM = 0.5f * (float)(M - 1);
-  const Cell c = locate(A, B, tau, M, hM);
+  const Cell c = locate<true>(A, B, tau, M, hM);
   float4 v[8];
   load_corners<BF16>(pay, (size_t)prim_of(A) * M * M * M + c.idx, M, v);
   if (FADE) {
@@ -421,7 +432,7 @@ __device__ __forceinline__ bool march_tile(const AccelView &av, int64_t u, int *
 }
 
 // 4 waves per SIMD: 5 spill and crowd the L1 (32768 x 16^3: 23 against 16 ms).
-template <bool BF16, bool FADE, bool SEQ>
+template <bool BF16, bool FADE, bool SEQ, bool BIG>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void k_march_fwd(
     AccelView av, const char *__restrict__ pay, const float *__restrict__ bg, float4 *__restrict__ rgba,
     mvp_ray_aux *__restrict__ aux, unsigned long long *__restrict__ counters, int64_t n_units) {
@@ -544,7 +555,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
             c.f[0] = u0 - q0;
             c.f[1] = u1 - q1;
             c.f[2] = u2 - q2;
-            c.idx = (int)fmaf(fmaf(q2, Mf, q1), Mf, q0);
+            c.idx = voxel_index<BIG>(q0, q1, q2, M, Mf);
             float4 vx[8];
             corners_at<BF16>((const char *)(pp[at][rl] + (uint64_t)(uint32_t)c.idx * kVox), row, slice, vx);
             if (FADE) {
@@ -706,13 +717,14 @@ hipError_t launch_march_fwd(const AccelView &av, const mvp_prims &p, const float
   const int grid = (int)std::min<int64_t>((units + kXcd - 1) / kXcd * kXcd, 1 << 22);   // a multiple of kXcd
   const bool fade = av.fade_alpha > 0.f;
   const size_t shm = fade ? (size_t)av.M * sizeof(float) : 0;
-#define MVP_FWD(B, F, S)                                                                                  \
-  hipLaunchKernelGGL((k_march_fwd<B, F, S>), dim3(grid), dim3(kWave), shm, s, av,                       \
+  const bool big = av.M > kFloatIndexM;
+#define MVP_FWD(B, F, S, I)                                                                               \
+  hipLaunchKernelGGL((k_march_fwd<B, F, S, I>), dim3(grid), dim3(kWave), shm, s, av,                    \
                      (const char *)p.payload, bg, (float4 *)rgba, aux, counters, units)
-#define MVP_FWD_S(B, F)               \
-  do {                                \
-    if (av.combine) MVP_FWD(B, F, true); \
-    else MVP_FWD(B, F, false);        \
+#define MVP_FWD_S(B, F)                                                               \
+  do {                                                                                \
+    if (av.combine) { if (big) MVP_FWD(B, F, true, true); else MVP_FWD(B, F, true, false); }   \
+    else { if (big) MVP_FWD(B, F, false, true); else MVP_FWD(B, F, false, false); }   \
   } while (0)
   if (p.payload_dtype == MVP_BF16) {
     if (fade) MVP_FWD_S(true, true); else MVP_FWD_S(true, false);
@@ -1087,6 +1099,7 @@ __device__ __forceinline__ void bwd_pair(const AccelView &av, const char *__rest
                                          int k, const float (&t)[3], const Slab &slab, GAcc *gdst, const LdsMap &lm, const FixedScale &fxs,
                                          const float *s_fade, bool pose,
                                          float (&P)[12], uint32_t &runs) {
+  constexpr bool kBig = !LDS_ACC;   // (a gradient in the LDS: M of at most 45)
   const int M = av.M;
   const float hM = 0.5f * (float)(M - 1);
   const float dt = av.step;
@@ -1162,7 +1175,7 @@ __device__ __forceinline__ void bwd_pair(const AccelView &av, const char *__rest
     int j = jr.x;
     Cell c;
     if (j <= jh) {
-      c = locate(A, B, (float)j * dt, M, hM);
+      c = locate<kBig>(A, B, (float)j * dt, M, hM);
       if (PREFETCH) load_cell(c.idx);
     }
     while (j <= jh) {
@@ -1207,7 +1220,7 @@ __device__ __forceinline__ void bwd_pair(const AccelView &av, const char *__rest
       // the next run's first sample, and its corners
       j = jl + 1;
       if (j <= jh) {
-        c = locate(A, B, (float)j * dt, M, hM);
+        c = locate<kBig>(A, B, (float)j * dt, M, hM);
         if (PREFETCH) load_cell(c.idx);
       }
   #pragma unroll
@@ -1309,7 +1322,7 @@ __device__ __forceinline__ void bwd_pair(const AccelView &av, const char *__rest
     int j = jr.x;
     Cell c;
     if (j <= jh) {
-      c = locate(A, B, (float)j * dt, M, hM);
+      c = locate<kBig>(A, B, (float)j * dt, M, hM);
       if (PREFETCH) load_cell(c.idx);
     }
     while (j <= jh) {
@@ -1396,7 +1409,7 @@ __device__ __forceinline__ void bwd_pair(const AccelView &av, const char *__rest
         H2 = fmaf(tau, gz, H2);
         ++j;
         if (j > jh) break;
-        c = locate(A, B, (float)j * dt, M, hM);
+        c = locate<kBig>(A, B, (float)j * dt, M, hM);
       } while (c.idx == cell);
       if (PREFETCH && j <= jh) load_cell(c.idx);
       // monomial adjoint -> corner adjoint (transpose of the basis change), on
