@@ -1867,9 +1867,7 @@ typedef void (*BwdItemsFn)(AccelView, const float *, const float *, const void *
 template <bool B, bool L, bool F, bool R>
 static BwdItemsFn bwd_items_fn(BwdShape shape) {
   if (shape == BwdShape::kThree) return k_bwd_items<B, L, F, R, 3, kTileThreads>;
-  if constexpr (R) {
-    if (shape == BwdShape::kSparse) return k_bwd_items<B, L, F, true, 1, kSparseThreads>;
-  }
+  if (shape == BwdShape::kSparse) return k_bwd_items<B, L, F, R, 1, kSparseThreads>;
   if constexpr (L) {
     if (shape == BwdShape::kSlabs) return k_bwd_items<B, L, F, R, 1, 2 * kTileThreads, true>;
     if (shape == BwdShape::kOne) return k_bwd_items<B, L, F, R, 1, 2 * kTileThreads>;
@@ -1954,7 +1952,12 @@ hipError_t launch_march_bwd(const AccelView &av, const mvp_prims &p, int64_t n_i
   // Device atomics in their place, 32 per cell run, ran at 46 G/s: 64 x 32^3 at
   // 667 x 1024 48.4 ms against 3.6.
   int slab_cells = 0;
-  if (g_pay && !in_lds) {
+  // The items' length was chosen at the build, for its payload size and way
+  // through a pair; this call's payload may be of another size.  Items of more
+  // than kItemEntries entries only fit the tables of the shape for sparse rays,
+  // which takes any payload and either way, but no slabs.
+  const bool sparse = av.item_entries > kItemEntries;
+  if (g_pay && !in_lds && !sparse) {
     const size_t layer = (size_t)p.M * p.M * 4 * sizeof(unsigned long long);
     const int layers = (int)((160 * 1024 - 2 * kStatic - fade_shm - 4096 * 3 - 64) / layer);
     if (layers >= 2) {
@@ -1972,7 +1975,6 @@ hipError_t launch_march_bwd(const AccelView &av, const mvp_prims &p, int64_t n_i
   // 3 waves per SIMD when 3 workgroups' LDS fits a CU; 512-thread workgroups
   // when only one does (16^3 payloads: 131 KB)
   const int wgs_fit = in_lds ? wgs_per_cu(lds) : 3;
-  const bool sparse = av.item_entries > kItemEntries;
   BwdShape shape = sparse ? BwdShape::kSparse : slab_cells ? BwdShape::kSlabs : wgs_fit >= 3 ? BwdShape::kThree : wgs_fit == 2 ? BwdShape::kTwo : BwdShape::kOne;
   auto wide = [&] { return shape == BwdShape::kOne || shape == BwdShape::kSlabs; };
   const int64_t n_slab = slab_cells ? (p.M - 2 + slab_cells) / slab_cells : 1;
