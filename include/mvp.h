@@ -152,10 +152,12 @@ const char *mvp_version(void);
  * sizes are known (one stream synchronisation).  The kernel that builds the
  * per-ray lists is launched by the build or, on large structures (see
  * mvp_accel_info), by the first mvp_render_fwd* or backward on the structure;
- * the lists the backward reads per primitive are built on the context's second
- * stream after that.  Calls on one
- * structure must be ordered on the caller's streams.  *out must be released
- * with mvp_accel_destroy. */
+ * the lists the backward reads per primitive are built after that, on the
+ * caller's stream or, large ones, on the context's second stream.  If that first
+ * call is being captured into a HIP graph, these lists are built at once, outside
+ * the graph, and the call (or a captured backward after it) BLOCKS until they
+ * are complete.  Calls on one structure must be ordered on the caller's streams.
+ * *out must be released with mvp_accel_destroy. */
 mvp_status mvp_build_accel(mvp_ctx *ctx, const mvp_prims *prims, const mvp_camera *cams,
                            int32_t n_views, const mvp_march_params *params,
                            mvp_accel **out, void *stream);

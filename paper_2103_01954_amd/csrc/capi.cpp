@@ -296,18 +296,38 @@ static mvp_status read_u64(const uint64_t *dev, uint64_t *host, hipStream_t s) {
   return MVP_OK;
 }
 
+// Whether work enqueued on s now is recorded into a graph.
+static bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;
+  }
+  return st != hipStreamCaptureStatusNone;
+}
+
+// Lets this thread run and wait for work on other streams while one of its
+// streams is captured.
+struct RelaxCapture {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  RelaxCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  ~RelaxCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
 // The transposed lists (primitive -> its culling-list entries) and the
 // backward work items; they need only the sorted culling lists.  Launched once,
 // by the first forward with per-ray state after its own launch or by the first
 // backward: on the context's side stream after the build's kernels (event
 // `built`), with `lists` recorded after them, or, where they take two short
 // kernels, on the caller's stream s, which saves the events between the streams.
-// The held temporaries are recycled after them.
-static mvp_status launch_lists(const mvp_accel *ac, hipStream_t s) {
+// Where s is captured they always run on the side stream, at once and not as
+// part of the graph: they are made once, from temporaries that are recycled
+// after them.
+static mvp_status launch_lists(const mvp_accel *ac, hipStream_t s, bool captured) {
   if (!ac->lists_pending.exchange(false)) return MVP_OK;
   mvp_accel *a = const_cast<mvp_accel *>(ac);
   mvp_ctx *ctx = a->ctx;
-  const bool beside = a->n_tile_pairs > 32768 || a->N > 8191;
+  const bool beside = captured || a->n_tile_pairs > 32768 || a->N > 8191;
   hipStream_t s2 = beside ? ctx->side : s;
   hipError_t e = beside ? hipStreamWaitEvent(s2, a->built, 0) : hipSuccess;
   if (e == hipSuccess)
@@ -747,20 +767,21 @@ mvp_status mvp_timing_stop(mvp_ctx *ctx) {
 
 // Whether counters are still as the build cleared them: once per structure, and
 // never while the stream is captured (a replay has to clear them itself).
-static bool still_clean(std::atomic<bool> &clean, hipStream_t s) {
-  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &st) != hipSuccess) {
-    (void)hipGetLastError();
-    st = hipStreamCaptureStatusActive;
-  }
-  return clean.exchange(false) && st == hipStreamCaptureStatusNone;
-}
+static bool still_clean(std::atomic<bool> &clean, bool captured) { return clean.exchange(false) && !captured; }
 
 // The per-ray pairs, if the build left them to the first forward or backward.
-static mvp_status pairs_ready(const mvp_accel *a, hipStream_t s) {
+// Where s is captured they are made at once on the side stream, and waited for,
+// so that the graph and calls outside it find them.
+static mvp_status pairs_ready(const mvp_accel *a, hipStream_t s, bool captured) {
   if (!a->pairs_pending.exchange(false)) return MVP_OK;
-  hipError_t e = launch_pairs(a->view(2), a->po, s);
-  if (e == hipSuccess) e = hipEventRecord(a->pairs_done, s);
+  hipStream_t s2 = captured ? a->ctx->side : s;
+  hipError_t e = captured ? hipStreamWaitEvent(s2, a->built, 0) : hipSuccess;
+  if (e == hipSuccess) e = launch_pairs(a->view(2), a->po, s2);
+  if (e == hipSuccess) e = hipEventRecord(a->pairs_done, s2);
+  if (e == hipSuccess && captured) {
+    RelaxCapture relax;
+    e = hipEventSynchronize(a->pairs_done);
+  }
   if (e != hipSuccess) a->pairs_pending.store(true);
   MVP_HIP(e);
   return MVP_OK;
@@ -771,21 +792,29 @@ static mvp_status render_fwd(mvp_ctx *ctx, const mvp_accel *a, const mvp_prims *
   MVP_CHECK(check_render(ctx, a, prims));
   if (!rgba && a->n_slots > 0) { set_error("rgba is NULL"); return MVP_ERR_INVALID; }
   MVP_HIP(hipSetDevice(ctx->device));
-  if (!still_clean(a->fwd_clean, s)) MVP_HIP(launch_zero_counters(a->counters, 0, kCntFwdPab + 1, s));
-  MVP_CHECK(pairs_ready(a, s));
+  const bool captured = capturing(s);
+  if (!still_clean(a->fwd_clean, captured)) MVP_HIP(launch_zero_counters(a->counters, 0, kCntFwdPab + 1, s));
+  MVP_CHECK(pairs_ready(a, s, captured));
   const auto ev = timer_slot(ctx, MVP_KERNEL_FWD_MARCH);
   if (ev.first) MVP_HIP(hipEventRecord(ev.first, s));
   MVP_HIP(launch_march_fwd(a->view(prims->M), *prims, bg, rgba, aux, a->counters, s));
   if (ev.second) MVP_HIP(hipEventRecord(ev.second, s));
-  return aux ? launch_lists(a, s) : MVP_OK;   // (without per-ray state no backward follows)
+  return aux ? launch_lists(a, s, captured) : MVP_OK;   // (without per-ray state no backward follows)
 }
 
 // What the backward reads of the structure: the pairs (built here if no
-// forward has built them) and the transposed lists (made on the side stream).
-static mvp_status bwd_ready(const mvp_accel *a, hipStream_t s) {
-  MVP_CHECK(pairs_ready(a, s));
-  MVP_CHECK(launch_lists(a, s));
-  if (a->lists_beside) MVP_HIP(hipStreamWaitEvent(s, a->lists, 0));
+// forward has built them) and the transposed lists.  A captured backward cannot
+// wait for work outside its graph, so the host does.
+static mvp_status bwd_ready(const mvp_accel *a, hipStream_t s, bool captured) {
+  MVP_CHECK(pairs_ready(a, s, captured));
+  MVP_CHECK(launch_lists(a, s, captured));
+  if (!a->lists_beside) return MVP_OK;
+  if (captured) {
+    RelaxCapture relax;
+    MVP_HIP(hipEventSynchronize(a->lists));
+  } else {
+    MVP_HIP(hipStreamWaitEvent(s, a->lists, 0));
+  }
   return MVP_OK;
 }
 
@@ -796,13 +825,14 @@ static mvp_status render_bwd(mvp_ctx *ctx, const mvp_accel *a, const mvp_prims *
   if (!a->for_backward) { set_error("the structure was built for the forward only"); return MVP_ERR_INVALID; }
   if ((!aux || !grad_rgba) && a->n_slots > 0) { set_error("aux and grad_rgba are required"); return MVP_ERR_INVALID; }
   MVP_HIP(hipSetDevice(ctx->device));
-  MVP_CHECK(bwd_ready(a, s));
+  const bool captured = capturing(s);
+  MVP_CHECK(bwd_ready(a, s, captured));
   Blocks temp{ctx, s};
   uint8_t *scratch = nullptr;
   MVP_CHECK(temp.get(&scratch, bwd_scratch_bytes(a->n_rays())));
   const auto ev = timer_slot(ctx, MVP_KERNEL_BWD_MARCH);
   MVP_HIP(launch_march_bwd(a->view(prims->M), *prims, a->n_items_max, aux, grad_rgba, bg, rgba, scratch, grad_payload,
-                           grad_pos, grad_rot, grad_scale, grad_bg, a->counters, still_clean(a->bwd_clean, s), s, ev.first,
+                           grad_pos, grad_rot, grad_scale, grad_bg, a->counters, still_clean(a->bwd_clean, captured), s, ev.first,
                            ev.second));
   return MVP_OK;   // the scratch is recycled after the kernels have run
 }
@@ -839,11 +869,12 @@ mvp_status mvp_render_bwd_noalloc(mvp_ctx *ctx, const mvp_accel *a, const mvp_pr
   void *ptr = (ctx->device >= 0 && ctx->device < kMaxDevices) ? g_scratch[ctx->device] : nullptr;
   if (!ptr) { set_error("the backward scratch array of device %d was not resolved", ctx->device); return MVP_ERR_DEVICE; }
   MVP_HIP(hipSetDevice(ctx->device));
-  MVP_CHECK(bwd_ready(a, (hipStream_t)stream));
+  const bool captured = capturing((hipStream_t)stream);
+  MVP_CHECK(bwd_ready(a, (hipStream_t)stream, captured));
   const auto ev = timer_slot(ctx, MVP_KERNEL_BWD_MARCH);
   MVP_HIP(launch_march_bwd(a->view(prims->M), *prims, a->n_items_max, aux, grad_rgba, nullptr, nullptr, ptr,
                            grad_payload, grad_pos, grad_rot, grad_scale, nullptr, a->counters,
-                           still_clean(a->bwd_clean, (hipStream_t)stream), (hipStream_t)stream, ev.first, ev.second));
+                           still_clean(a->bwd_clean, captured), (hipStream_t)stream, ev.first, ev.second));
   return MVP_OK;
 }
 
