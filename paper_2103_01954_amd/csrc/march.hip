@@ -583,13 +583,13 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
       }
       n_cell += cnt;
       // Composite the window's samples in order (a sample outside every
-      // primitive adds 0).  Opacities are not negative, so a ray stops in this
-      // window iff its last sum exceeds the limit.
+      // primitive adds 0).  Where none of its opacities is negative, a ray stops
+      // in this window iff its last sum exceeds the limit.
       const float x = as * dt;
       float Tw = T, J0 = I0, J1c = I1, J2 = I2;
       window_steps(Tw, J0, J1c, J2, x, ar, ag, ab, dt);
       const bool mine = cnt > 0;
-      if (!ballot(act && !(Tw <= lim))) {   // no ray of the wave stops here
+      if (!ballot(act && (!(Tw <= lim) || x < 0.f))) {   // no ray of the wave stops here
         T = Tw;
         I0 = J0;
         I1 = J1c;
