@@ -633,7 +633,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
             T = Tn;
             if (!over) {
               act = ws == kWin;
-            } else if (!SEQ) {
+            } else if (!SEQ || !(tw > 1.0f)) {   // (NaN: under either rule the whole sample's)
               const float wgt = (1.0f - T) / ss;
               I0 = fmaf(s0, wgt, I0);
               I1 = fmaf(s1, wgt, I1);

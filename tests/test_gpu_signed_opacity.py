@@ -7,6 +7,7 @@ primitive (a sample of several is taken one by one only if its sum
 saturates)."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
 from gpu_util import max_abs, say
@@ -39,3 +40,20 @@ def test_negative_opacity(mvp_ctx, combine, n, size):
     if sure.all():
         assert rs == ref["ray_samples"].sum() and ps == ref["prim_samples"].sum()
 
+
+
+def test_nan_opacity(mvp_ctx):
+    """A NaN density makes a ray's colour NaN, under both combine rules alike."""
+    prims = scenes.random_box_scene(1011, n=8, m=6, s_lo=0.3, s_hi=0.6)
+    prims.payload[..., 3] *= np.float32(0.5)
+    prims.payload[2, 2:4, 2:4, 2:4, 3] = np.nan
+    cam = scenes.look_at_camera(np.random.default_rng(1012), 40, 30)
+    dp = DevicePrims.from_host(prims)
+    nan = {}
+    for combine in ("sum", "sequential"):
+        acc = mvp_ctx.build_accel(dp, [cam], scenes.MarchParams(1.0 / 64, 1e-6, combine=combine))
+        nan[combine] = torch.isnan(acc.render_fwd(dp)[0])
+        acc.destroy()
+    say(f"{int(nan['sum'].any(-1).sum())} rays with a NaN")
+    assert int(nan["sum"][..., :3].any(-1).sum()) > 5
+    assert torch.equal(nan["sum"], nan["sequential"])
