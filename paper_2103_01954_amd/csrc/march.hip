@@ -1137,6 +1137,7 @@ __device__ __forceinline__ void bwd_pair(const AccelView &av, const char *__rest
   const bool mx = m & 1u, my = (m >> 1) & 1u, mz = (m >> 2) & 1u;
   const float sgx = mx ? -1.0f : 1.0f, sgy = my ? -1.0f : 1.0f, sgz = mz ? -1.0f : 1.0f;
   const float offx = mx ? 1.0f : 0.0f, offy = my ? 1.0f : 0.0f, offz = mz ? 1.0f : 0.0f;
+  const float hMx = sgx * hM, hMy = sgy * hM, hMz = sgz * hM;
   // byte offsets of the register slots' voxels in the primitive's payload
   constexpr int kVox = BF16 ? 8 : 16;
   const int MMi = M * M;
@@ -1192,9 +1193,12 @@ __device__ __forceinline__ void bwd_pair(const AccelView &av, const char *__rest
       const int L = jl - j + (sp ? 0 : 1);         // ordinary samples of the run
       const float jm = 0.5f * (float)(j + j + L - 1);   // their middle
       const float tm = jm * dt;
-      const float x = fmaf(sgx, fmaf(fmaf(tm, B.x, A.x), hM, hM) - (float)ci0, offx),
-                  y = fmaf(sgy, fmaf(fmaf(tm, B.y, A.y), hM, hM) - (float)ci1, offy),
-                  z = fmaf(sgz, fmaf(fmaf(tm, B.z, A.z), hM, hM) - (float)ci2, offz);
+      // offsets from the cell's own corner ((M-1)/2 - index is exact): rounded once,
+      // at their own size, where the whole coordinate's rounding would be shared by
+      // all of the run's samples
+      const float x = fmaf(fmaf(tm, B.x, A.x), hMx, fmaf(sgx, hM - (float)ci0, offx)),
+                  y = fmaf(fmaf(tm, B.y, A.y), hMy, fmaf(sgy, hM - (float)ci1, offy)),
+                  z = fmaf(fmaf(tm, B.z, A.z), hMz, fmaf(sgz, hM - (float)ci2, offz));
       if (FADE) {
         const float wx[2] = {s_fade[ci0 + (mx ? 1 : 0)], s_fade[ci0 + (mx ? 0 : 1)]};
         const float wy[2] = {s_fade[ci1 + (my ? 1 : 0)], s_fade[ci1 + (my ? 0 : 1)]};
@@ -1439,7 +1443,6 @@ __device__ __forceinline__ void bwd_pair(const AccelView &av, const char *__rest
   // loop (tref = 0) sum x_m dL/dy_i = o_m G_i + d_m H_i; the primitive's A, t, R
   // and s are applied once per item (pose_from_sums).
   const DevCam &cam = av.cams[rv];
-  const float hMx = sgx * hM, hMy = sgy * hM, hMz = sgz * hM;
   const float G[3] = {hMx * G0, hMy * G1, hMz * G2}, H[3] = {hMx * H0, hMy * H1, hMz * H2};
 #pragma unroll
   for (int mm = 0; mm < 3; ++mm) {
