@@ -952,12 +952,13 @@ __host__ __device__ inline LdsMap lds_map(int M, bool padded) {
 // complement word that the LDS atomic adds.  (Rounding down v + 1/2, formed in
 // one fma, saves an instruction but is biased where v has no fraction bits left.)
 //
-// WIDE (payloads taken in slabs, sparse rays): |v| < 2^44, converted in two
+// WIDE (payloads taken in slabs, sparse rays): |v| < 2^50, converted in two
 // exact parts.  The scale follows the largest bound of an item's pairs, which
 // may be thousands of times what most voxels get (a ray that saturates in a
 // faint sample): with 30 bits the rounding of every addend then shows in the
-// gradient (970 x 24^3 with the fade window: over 1e-6 of it), with 44 bits only
-// the FP32 rounding of the run's own sums is left.
+// gradient (970 x 24^3 with the fade window: over 1e-6 of it), with 50 bits only
+// the FP32 rounding of the run's own sums is left (the voxels beside one ray with 2^18
+// times the others' upstream gradient: under 2e-6, 3e-6 to 7e-6 with 44 bits).
 template <bool WIDE>
 __device__ __forceinline__ unsigned long long fixed_addend(float v) {
   if constexpr (WIDE) {
@@ -1515,20 +1516,22 @@ __device__ __forceinline__ int pair_len(const AccelView &av, const mvp_ray_aux *
   return n;
 }
 
-// Fixed-point scale of a work item none of whose pairs adds more than `bound`
-// to any one gradient value.  A cell run adds part of one pair's share, so
-// with the scale below every addend is under 2^29 (half of that covers the
-// rounding of the run's sums) and fits 32 bits; an item has at most
-// 128 entries x 256 rays = 2^15 pairs, so a 64-bit sum stays under 2^44 (WIDE:
-// addends under 2^43, sums under 2^58).
+// Fixed-point scale of a work item of `total` pairs none of which adds more than
+// `bound` to any one gradient value.  A cell run adds part of one pair's share,
+// so with the scale below every addend is under 2^29 (half of that covers the
+// rounding of the run's sums) and fits 32 bits; an item has at most 128
+// entries x 256 rays = 2^15 pairs, so a 64-bit sum stays under 2^44.  WIDE:
+// addends under 2^49, or less where so many pairs could take a sum past 2^62
+// (more than 2^13).
 // 0 for a non-finite bound (the item's gradient is then written as NaN).
 template <bool WIDE>
-__device__ __forceinline__ float fixed_scale(float bound) {
+__device__ __forceinline__ float fixed_scale(float bound, uint32_t total) {
   if (!(bound < INFINITY)) return 0.0f;
   if (!(bound > 0.0f)) return 1.0f;
+  const int bits = WIDE ? min(50, 63 - (32 - __clz((int)total))) : 30;   // 32 - clz: total < 2^(32 - clz)
   int e;
   (void)frexpf(2.0f * bound, &e);   // 2 bound = m 2^e, 0.5 <= m < 1, so bound < 2^(e-1)
-  return ldexpf(1.0f, min(max((WIDE ? 44 : 30) - e, -126), 126));
+  return ldexpf(1.0f, min(max(bits - e, -126), 126));
 }
 
 // Length classes for ordering pairs: exact below 32 samples, then 4 wide.
@@ -1706,7 +1709,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES))
       bound = 0.f;
 #pragma unroll
       for (int w = 0; w < THREADS / kWave; ++w) bound = nan_max(bound, s_bnd[w]);
-      fscale = fixed_scale<kWide>(bound);
+      fscale = fixed_scale<kWide>(bound, total);
       if (LDS_ACC) fxs = split_scale(fscale);
       if (wave == 0) {   // exclusive scan over the classes from the longest down
         const uint32_t c = s_cls[kLenBuckets - 1 - lane];
@@ -1797,7 +1800,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES))
         bound = 0.f;
 #pragma unroll
         for (int w = 0; w < THREADS / kWave; ++w) bound = nan_max(bound, s_bnd[w]);
-        fscale = fixed_scale<kWide>(bound);
+        fscale = fixed_scale<kWide>(bound, total);
       if (LDS_ACC) fxs = split_scale(fscale);
       }
       for (uint32_t i = i0, q = q0; i < iend; i += stride) {
