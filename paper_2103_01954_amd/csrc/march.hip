@@ -2023,15 +2023,16 @@ hipError_t launch_march_bwd(const AccelView &av, const mvp_prims &p, int64_t n_i
 
 // Entries per backward work item.
 //
-// Closed-form runs: a long item zeroes and flushes its primitive's gradient
-// less often and fills its waves better (rays spread over 4096 tiles, 1 ray
-// each: 786 us with 32 entries, 518 with 64); but where there are few
-// primitives, long items leave workgroups idle at the end (512 of 16^3, 56
-// entries each, one workgroup per CU: 1953 us with 64 entries, 1625 with 32, 1315
-// with 16, 1388 with 8).  So an item takes 64 entries, or fewer where that is
-// under 8 items for each workgroup that is resident at once; not under 32 for
-// payloads up to 8^3, where it does not pay (4096 of them at 667 x 1024: 690 us
-// with 64 and 32, 699 with 16).
+// Up to 8^3: 32.  The scale of the 30-bit sums follows the item's largest pair,
+// so a longer item leaves the others fewer bits, and it is no faster either (4096 of
+// them at 4 x 1024^2: a step of 12.36 ms with 32, 12.47 with 64; at 667 x 1024 the
+// backward takes 690 us with both and 699 with 16).
+//
+// To 16^3 with closed-form runs: a long item zeroes and flushes its primitive's
+// gradient less often, but where there are few primitives, long items leave
+// workgroups idle at the end (512 of 16^3, 56 entries each, one workgroup per CU:
+// 1953 us with 64 entries, 1625 with 32, 1315 with 16, 1388 with 8).  So an item
+// takes 64 entries, or fewer, down to 16, where that is under 8 items for each CU.
 //
 // Sparse rays (n_slots, the rays of all entries' tiles, few per entry) leave
 // most of 256 threads without a pair: 128 entries for 64 threads, of which
@@ -2050,9 +2051,9 @@ int backward_item_entries(const AccelView &av, int M, uint64_t n_entries, uint64
   if (M > 16) return 16;
   if (!backward_by_runs(av, M)) return M <= 8 ? 32 : kItemEntries;
   if (M <= kSparseMaxM && n_slots < (M <= 8 ? 8 : 5) * n_entries) return kSparseEntries;
-  const uint64_t want = 8 * 256 * (M <= 8 ? 3 : 1);
+  if (M <= 8) return 32;
   int n = kItemEntries;
-  while (n > (M <= 8 ? 32 : 16) && n_entries / n + (uint64_t)av.N < want) n /= 2;
+  while (n > 16 && n_entries / n + (uint64_t)av.N < 8 * 256) n /= 2;
   return n;
 }
 
