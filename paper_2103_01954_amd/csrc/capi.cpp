@@ -516,6 +516,7 @@ mvp_status build_accel(mvp_ctx *ctx, const mvp_prims *prims, const mvp_camera *c
   MVP_HIP(launch_segment_sort(a->tile_off, a->tile_list, (int64_t)ntile, depth, N, tx * ty, s));
   a->item_entries = backward_item_entries(av, prims->M, n_tile_pairs, capacity);
   a->n_items_max = for_backward ? (int64_t)(n_tile_pairs / a->item_entries) + N : 0;
+  if (for_backward) MVP_CHECK(keep.get(&a->item_lists, (size_t)a->n_items_max + 2));
   // Every ray's pairs, the entry frames and the per-entry pair lists: by the
   // pairs kernel now, with the transposed lists beside it, or, where the march
   // is long enough to hide those (8192 tiles of payloads of at most 8^3), with
@@ -539,7 +540,7 @@ mvp_status build_accel(mvp_ctx *ctx, const mvp_prims *prims, const mvp_camera *c
   a->pair_capacity = capacity;
   a->bytes = (int64_t)(n_views * sizeof(DevCam) + 3 * (size_t)N * 16 + 2 * (ntile + 1) * 8 + R * 16 +
                        kCntSlots * kCntStride * 8 +
-                       (for_backward ? n_tile_pairs * (4 + 4 + 48 + 8 + 16 + 4) + (size_t)N * 24 + capacity * 24
+                       (for_backward ? n_tile_pairs * (4 + 4 + 48 + 8 + 16 + 4) + (size_t)N * 24 + capacity * 24 + (a->n_items_max + 2) * 4
                                      : n_tile_pairs * (4 + 48) + capacity * 16) +
                        (rays ? R * 12 + (ntile + 1) * 8 : 0));
   a->blocks = keep.list;

@@ -105,7 +105,7 @@ struct mvp_accel {
   uint64_t *prim_entry_off = nullptr;
   uint32_t *prim_entries = nullptr;
   uint64_t *item_off = nullptr;
-  uint32_t *item_prim = nullptr;
+  uint32_t *item_prim = nullptr, *item_lists = nullptr;
   int64_t n_items_max = 0;             // upper bound on the backward work items
   int32_t item_entries = 64;           // culling-list entries per backward work item
   float max_dist_ratio = 0.f, max_inv_scale = 0.f;   // over the boxes (see AccelView)
@@ -159,6 +159,7 @@ struct mvp_accel {
     v.fade_alpha = params.fade_alpha; v.fade_beta = params.fade_beta; v.combine = params.combine;
     v.cams = cams; v.xf = xf; v.tile_off = tile_off; v.tile_list = tile_list;
     v.prim_entry_off = prim_entry_off; v.prim_entries = prim_entries; v.item_off = item_off; v.item_prim = item_prim;
+    v.item_lists = item_lists;
     v.item_entries = item_entries;
     v.max_dist_ratio = max_dist_ratio; v.max_inv_scale = max_inv_scale;
     v.ef = ef; v.pair_base = pair_base; v.ray_seg = ray_seg; v.ray_nj = ray_nj; v.pr = pr;

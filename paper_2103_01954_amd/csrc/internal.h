@@ -87,6 +87,7 @@ struct AccelView {
   const uint32_t *prim_entries;    // [n_tile_pairs]
   const uint64_t *item_off;        // [N+1], over the primitives in the order item_prim
   const uint32_t *item_prim;       // [N] the backward's order of the primitives
+  uint32_t *item_lists;            // [2 + work items] scratch of the backward (k_item_split)
   const float4 *ef;            // [3 n_tile_pairs]
   const uint64_t *pair_base;   // [V*T+1]
   const uint64_t *ray_seg;     // [R]

@@ -776,6 +776,7 @@ __global__ __launch_bounds__(256) void k_bwd_rays(AccelView av, const void *__re
   __shared__ uint32_t s_clamped[kBwdRaysPerBlock];
   __shared__ int s_nc;
   if (threadIdx.x == 0) s_nc = 0;
+  if (blockIdx.x == 0 && threadIdx.x < 2) av.item_lists[threadIdx.x] = 0u;   // (for k_item_split)
   if (FADE) fill_fade(s_fade, av.M, av.fade_alpha, av.fade_beta);
   __syncthreads();
   const float cmax = __uint_as_float(pmax[0]), smax = __uint_as_float(pmax[1]);
@@ -1038,6 +1039,8 @@ __device__ __forceinline__ LineFn along(const float (&F)[8], float x, float y, f
   f.c3 = F[7] * pqr;
   return f;
 }
+
+constexpr unsigned kSlabGrid = 4096;   // workgroups over the listed items (most may not be there)
 
 // Longest run taken at once (a longer one is taken in parts).
 constexpr int kRunMax = 64;
@@ -1534,6 +1537,54 @@ __device__ __forceinline__ float fixed_scale(float bound, uint32_t total) {
   return ldexpf(1.0f, min(max(bits - e, -126), 126));
 }
 
+// Payloads taken in slabs: which work items are worth it.  Every slab of an item
+// costs its workgroup some 16 us however few pairs there are (128 KB of LDS to
+// clear and to read back, one workgroup per CU), a pair taken with device
+// atomics some 13 ns of the device.  The items of at least `few` pairs are listed
+// from the front of item_lists, the others (if they have any) from its back, and
+// the latter go to device memory where they would be more than kSlabsAtLeast slabs
+// (about eight for each CU; fewer are hidden better than another kernel's
+// latency).  64 x 32^3, 1000 rays: backward of 300 us, 3000 all in slabs; 4000 x
+// 32^3 at 64 x 64: 1.5 against 6.4 ms.
+constexpr uint32_t kSlabsAtLeast = 2048;
+__global__ __launch_bounds__(kWave) void k_item_split(AccelView av, uint32_t few, uint32_t n_list) {
+  const uint32_t it = blockIdx.x * (uint32_t)kWave + threadIdx.x;
+  uint32_t total = 0;
+  if (it < av.item_off[av.N]) {
+    int lo = 0, hi = av.N - 1;   // primitive of the item: the p-th in item order, last p with item_off[p] <= it
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (av.item_off[mid] <= it) lo = mid; else hi = mid - 1;
+    }
+    const uint32_t k = av.item_prim[lo];
+    const uint64_t eb = av.prim_entry_off[k] + (it - av.item_off[lo]) * (uint64_t)av.item_entries;
+    const int nent = (int)min<uint64_t>((uint64_t)av.item_entries, av.prim_entry_off[k + 1] - eb);
+    constexpr int kB = 16;   // entries asked for together
+    for (int q0 = 0; q0 < nent; q0 += kB) {
+      uint32_t g[kB];
+      uint4 c[kB];
+#pragma unroll
+      for (int q = 0; q < kB; ++q) g[q] = av.prim_entries[eb + min(q0 + q, nent - 1)];
+#pragma unroll
+      for (int q = 0; q < kB; ++q) c[q] = ((const uint4 *)av.ent_n)[g[q]];
+#pragma unroll
+      for (int q = 0; q < kB; ++q) total += q0 + q < nent ? c[q].x + c[q].y + c[q].z + c[q].w : 0u;
+    }
+  }
+  const int lane = threadIdx.x;
+  const unsigned long long lt = (1ull << lane) - 1ull;
+  const unsigned long long many = __ballot(total >= few), some = __ballot(total > 0 && total < few);
+  uint32_t at_many = 0, at_some = 0;
+  if (lane == 0) {
+    if (many) at_many = atomicAdd(&av.item_lists[0], (uint32_t)__popcll(many));
+    if (some) at_some = atomicAdd(&av.item_lists[1], (uint32_t)__popcll(some));
+  }
+  at_many = __builtin_amdgcn_readfirstlane(at_many);
+  at_some = __builtin_amdgcn_readfirstlane(at_some);
+  if (total >= few) av.item_lists[2 + at_many + (uint32_t)__popcll(many & lt)] = it;
+  else if (total > 0) av.item_lists[2 + n_list - 1 - (at_some + (uint32_t)__popcll(some & lt))] = it;
+}
+
 // Length classes for ordering pairs: exact below 32 samples, then 4 wide.
 __device__ __forceinline__ int len_bucket(int n) { return n < 32 ? n : min(kLenBuckets - 1, 32 + ((n - 32) >> 2)); }
 
@@ -1553,7 +1604,7 @@ template <bool BF16, bool LDS_ACC, bool FADE, bool RUNS, int WAVES, int THREADS,
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES))) void k_bwd_items(
     AccelView av, const float *__restrict__ rot, const float *__restrict__ scale, const void *__restrict__ pay,
     const mvp_ray_aux *__restrict__ aux, const float4 *__restrict__ grad_rgba, const RayConst *__restrict__ rc,
-    const RayBound *__restrict__ rbd, BwdOut out, uint32_t sort_cap, int padded, int slab_cells,
+    const RayBound *__restrict__ rbd, BwdOut out, uint32_t sort_cap, int padded, int slab_cells, uint32_t n_list,
     unsigned long long *__restrict__ counters) {
   // loads of this thread: pairs visited by the ordering / bound pass, pairs
   // replayed, their cell runs (one voxel-corner set each), and the non-zero
@@ -1597,12 +1648,23 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES))
     fill_fade(s_fade, M, av.fade_alpha, av.fade_beta);
     __syncthreads();
   }
-  const uint64_t n_items = av.item_off[av.N] * n_slab;
+  // n_list > 0: the items of k_item_split's lists (of at most n_list items)
+  uint32_t n_many = 0, n_few = 0;
+  if ((SLABS || !LDS_ACC) && n_list) {
+    n_many = av.item_lists[0];
+    n_few = av.item_lists[1];
+    const uint32_t slabs = (uint32_t)((M - 2 + slab_cells) / slab_cells);
+    if (((uint64_t)n_few * slabs <= kSlabsAtLeast) != SLABS) n_few = 0;   // they are the other kernel's
+    if (!SLABS) n_many = 0;
+  }
+  const bool listed = (SLABS || !LDS_ACC) && n_list;
+  const uint64_t n_items = (listed ? (uint64_t)n_many + n_few : av.item_off[av.N]) * n_slab;
   for (uint64_t is = blockIdx.x; is < n_items; is += gridDim.x) {
-    const uint64_t it = SLABS ? is / n_slab : is;
+    uint64_t it = SLABS ? is / n_slab : is;
+    if (listed) it = av.item_lists[2 + (it < n_many ? it : n_list - 1 - (it - n_many))];
     Slab slab{0, M - 1};
     if (SLABS) {
-      slab.z0 = (int)(is - it * n_slab) * slab_cells;
+      slab.z0 = (int)(is % n_slab) * slab_cells;
       slab.z1 = min(slab.z0 + slab_cells, M - 1);
     }
     if (threadIdx.x == 0) {   // primitive of the item: the p-th in item order, last p with item_off[p] <= it
@@ -1869,7 +1931,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES))
 // threads, one of 512 threads in slabs, or of 64 threads for sparse rays.
 enum class BwdShape { kThree, kTwo, kOne, kSlabs, kSparse };
 typedef void (*BwdItemsFn)(AccelView, const float *, const float *, const void *, const mvp_ray_aux *, const float4 *,
-                           const RayConst *, const RayBound *, BwdOut, uint32_t, int, int, unsigned long long *);
+                           const RayConst *, const RayBound *, BwdOut, uint32_t, int, int, uint32_t, unsigned long long *);
 template <bool B, bool L, bool F, bool R>
 static BwdItemsFn bwd_items_fn(BwdShape shape) {
   if (shape == BwdShape::kThree) return k_bwd_items<B, L, F, R, 3, kTileThreads>;
@@ -1984,7 +2046,9 @@ hipError_t launch_march_bwd(const AccelView &av, const mvp_prims &p, int64_t n_i
   BwdShape shape = sparse ? BwdShape::kSparse : slab_cells ? BwdShape::kSlabs : wgs_fit >= 3 ? BwdShape::kThree : wgs_fit == 2 ? BwdShape::kTwo : BwdShape::kOne;
   auto wide = [&] { return shape == BwdShape::kOne || shape == BwdShape::kSlabs; };
   const int64_t n_slab = slab_cells ? (p.M - 2 + slab_cells) / slab_cells : 1;
-  const unsigned grid = (unsigned)std::min<int64_t>(n_items_max * n_slab, 1 << 20);
+  // items of few pairs are left out of the slabs where there may be many of them
+  uint32_t n_list = n_items_max * n_slab > kSlabsAtLeast && slab_cells ? (uint32_t)n_items_max : 0u;
+  const unsigned grid = (unsigned)std::min<int64_t>(n_items_max * n_slab, n_list ? kSlabGrid : 1 << 20);
   BwdOut out{g_pay, g_pos, g_rot, g_scale};
   size_t shm = (in_lds ? lds : 0) + fade_shm;
   // the pair-ordering buffer takes what is left of the LDS share of a
@@ -2008,14 +2072,24 @@ hipError_t launch_march_bwd(const AccelView &av, const mvp_prims &p, int64_t n_i
       // gradients straight to device memory, pairs in list order
       shape = sparse ? BwdShape::kSparse : BwdShape::kThree;
       slab_cells = 0;
+      n_list = 0;
       sort_cap = 0;
       shm = fade_shm;
       fn = bwd_items_fn(bf16, false, fade, runs, shape);
     }
   }
   if (t0) (void)hipEventRecord(t0, s);
+  if (n_list) {
+    const uint32_t few = (uint32_t)std::min<int64_t>(20 + 4 * n_slab, 100);
+    hipLaunchKernelGGL(k_item_split, dim3((unsigned)((n_items_max + kWave - 1) / kWave)), dim3(kWave), 0, s, av, few, n_list);
+    hipLaunchKernelGGL(bwd_items_fn(bf16, false, fade, runs, BwdShape::kThree), dim3(grid), dim3(kTileThreads),
+                       fade_shm + kTileThreads * (sizeof(uint16_t) + 1), s, av, p.rot, p.scale, p.payload, aux,
+                       (const float4 *)grad_rgba, rc, rbd, out, (uint32_t)kTileThreads, 0, slab_cells, n_list, counters);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
   hipLaunchKernelGGL(fn, dim3(grid), dim3(sparse ? kSparseThreads : wide() ? 2 * kTileThreads : kTileThreads), shm, s, av, p.rot, p.scale, p.payload,
-                     aux, (const float4 *)grad_rgba, rc, rbd, out, sort_cap, padded, slab_cells, counters);
+                     aux, (const float4 *)grad_rgba, rc, rbd, out, sort_cap, padded, slab_cells, n_list, counters);
   e = hipGetLastError();
   if (t1) (void)hipEventRecord(t1, s);
   return e;
