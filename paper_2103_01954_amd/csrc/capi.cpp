@@ -465,8 +465,8 @@ mvp_status build_accel(mvp_ctx *ctx, const mvp_prims *prims, const mvp_camera *c
   // culling lists: rectangles, tile counts, offsets; pair capacities; one
   // stream synchronisation for the sizes
   MVP_HIP(launch_prep(*prims, av, a->xf, rect, depth, tile_cnt, a->counters, s));
-  uint64_t host_sz[5] = {0, 0, 0, 0, 0};
-  uint64_t *dsz = (uint64_t *)a->counters + kCntSizes;
+  uint64_t host_sz[6] = {0, 0, 0, 0, 0, 0};
+  uint64_t *dsz = (uint64_t *)a->counters + kCntHost;
   uint64_t *hsz = pin.p ? (uint64_t *)pin.p : host_sz;   // the pinned block is written by the last kernel itself
   MVP_HIP(launch_tile_offsets(tile_cnt, rcnt, ntile, a->tile_off, a->pair_base, flag, a->counters, pin.p ? hsz : dsz,
                               scratch, s));
@@ -479,6 +479,7 @@ mvp_status build_accel(mvp_ctx *ctx, const mvp_prims *prims, const mvp_camera *c
     const uint32_t b0 = (uint32_t)hsz[3], b1 = (uint32_t)hsz[4];
     memcpy(&a->max_dist_ratio, &b0, 4);
     memcpy(&a->max_inv_scale, &b1, 4);
+    a->full_tiles = (int64_t)hsz[5];
   }
   if (flag_h & 1u) { set_error("a ray pixel id is outside [0, n_views*height*width)"); return MVP_ERR_INVALID; }
   if (flag_h & 2u) { set_error("more than 256 rays in one 16x16 tile (repeated pixel ids)"); return MVP_ERR_INVALID; }

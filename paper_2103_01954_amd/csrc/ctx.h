@@ -109,6 +109,7 @@ struct mvp_accel {
   int64_t n_items_max = 0;             // upper bound on the backward work items
   int32_t item_entries = 64;           // culling-list entries per backward work item
   float max_dist_ratio = 0.f, max_inv_scale = 0.f;   // over the boxes (see AccelView)
+  int64_t full_tiles = 0;
   float4 *ef = nullptr;                // entry frames
   uint64_t *pair_base = nullptr;       // per tile
   uint64_t *ray_seg = nullptr;         // per ray slot
@@ -162,6 +163,7 @@ struct mvp_accel {
     v.item_lists = item_lists;
     v.item_entries = item_entries;
     v.max_dist_ratio = max_dist_ratio; v.max_inv_scale = max_inv_scale;
+    v.full_tiles = full_tiles;
     v.ef = ef; v.pair_base = pair_base; v.ray_seg = ray_seg; v.ray_nj = ray_nj; v.pr = pr;
     v.ent_base = ent_base; v.ent_n = ent_n; v.ent_tile = ent_tile; v.ent_rec = ent_rec;
     v.n_slots = n_slots; v.ray_pix = ray_pix; v.tile_ray_off = tile_ray_off; v.tile_rays = tile_rays;

@@ -249,15 +249,16 @@ __device__ __forceinline__ uint64_t tile_capacity(uint32_t len, const uint32_t *
   return c > 0xffffffffull ? 0xffffffffull : c;   // integer compare (no FP64 on the device)
 }
 
-// the build's sizes, for the host: entries, capacity, ray-subset flags, and the
-// two statistics of the boxes (kCntSizes + 3, + 4, from k_prep)
-__device__ __forceinline__ void write_sizes(uint64_t *out, uint64_t entries, uint64_t capacity, const uint32_t *flag,
-                                            const unsigned long long *counters) {
+// the build's sizes, for the host: entries, capacity, ray-subset flags, the two
+// statistics of the boxes (kCntSizes + 3, + 4, from k_prep) and the tiles with entries
+__device__ __forceinline__ void write_sizes(uint64_t *out, uint64_t entries, uint64_t capacity, uint64_t full,
+                                            const uint32_t *flag, const unsigned long long *counters) {
   out[0] = entries;
   out[1] = capacity;
   out[2] = flag ? (uint64_t)*flag : 0ull;
   out[3] = counters[kCntSizes + 3];
   out[4] = counters[kCntSizes + 4];
+  out[5] = full;
   __threadfence_system();   // out may be pinned host memory
 }
 
@@ -293,8 +294,11 @@ __global__ __launch_bounds__(kScanOneThreads) void k_tile_offsets_one(const uint
                                                                       const uint32_t *__restrict__ flag,
                                                                       const unsigned long long *__restrict__ counters,
                                                                       uint64_t *sizes) {
+  __shared__ uint32_t s_full;
+  if (threadIdx.x == 0) s_full = 0;
+  __syncthreads();
   const size_t t0 = (size_t)threadIdx.x * kScanOneBatch;
-  uint32_t len[kScanOneBatch];
+  uint32_t len[kScanOneBatch], full = 0;
   uint64_t cap[kScanOneBatch], a = 0, b = 0;
 #pragma unroll
   for (int i = 0; i < kScanOneBatch; ++i) {
@@ -302,9 +306,11 @@ __global__ __launch_bounds__(kScanOneThreads) void k_tile_offsets_one(const uint
     cap[i] = t0 + i < n ? tile_capacity(len[i], rays, t0 + i) : 0ull;
     a += len[i];
     b += cap[i];
+    full += (uint32_t)__popcll(__ballot(len[i] != 0));
   }
+  if ((threadIdx.x & (kWave - 1)) == 0) atomicAdd(&s_full, full);
   uint64_t ta, tb;
-  block_scan2<kScanOneThreads / kWave>(a, b, ta, tb);
+  block_scan2<kScanOneThreads / kWave>(a, b, ta, tb);   // (its barriers order s_full)
 #pragma unroll
   for (int i = 0; i < kScanOneBatch; ++i) {
     if (t0 + i < n) {
@@ -317,7 +323,7 @@ __global__ __launch_bounds__(kScanOneThreads) void k_tile_offsets_one(const uint
   if (threadIdx.x == 0) {
     off[n] = ta;
     base[n] = tb;
-    write_sizes(sizes, ta, tb, flag, counters);
+    write_sizes(sizes, ta, tb, s_full, flag, counters);
   }
 }
 
@@ -327,9 +333,10 @@ template <bool WRITE>
 __global__ __launch_bounds__(kScanThreads) void k_tile_offsets(const uint32_t *__restrict__ cnt,
                                                                const uint32_t *__restrict__ rays, size_t n,
                                                                uint64_t *__restrict__ part, uint64_t *__restrict__ off,
-                                                               uint64_t *__restrict__ base) {
+                                                               uint64_t *__restrict__ base,
+                                                               unsigned long long *__restrict__ counters) {
   const size_t t0 = (size_t)blockIdx.x * kScanBlock + (size_t)threadIdx.x * kScanItems;
-  uint32_t len[kScanItems];
+  uint32_t len[kScanItems], full = 0;
   uint64_t cap[kScanItems], a = 0, b = 0;
 #pragma unroll
   for (int i = 0; i < kScanItems; ++i) {
@@ -337,6 +344,7 @@ __global__ __launch_bounds__(kScanThreads) void k_tile_offsets(const uint32_t *_
     cap[i] = t0 + i < n ? tile_capacity(len[i], rays, t0 + i) : 0ull;
     a += len[i];
     b += cap[i];
+    full += (uint32_t)__popcll(__ballot(len[i] != 0));
   }
   uint64_t ta, tb;
   block_scan2<kScanThreads / kWave>(a, b, ta, tb);
@@ -345,6 +353,7 @@ __global__ __launch_bounds__(kScanThreads) void k_tile_offsets(const uint32_t *_
       part[2 * blockIdx.x] = ta;
       part[2 * blockIdx.x + 1] = tb;
     }
+    if ((threadIdx.x & (kWave - 1)) == 0) atomicAdd(&counters[kCntTiles], (unsigned long long)full);
     return;
   }
   a += part[2 * blockIdx.x];
@@ -385,14 +394,14 @@ __global__ __launch_bounds__(kScanOneThreads) void k_tile_offsets_parts(uint64_t
   if (threadIdx.x == 0) {
     off[n] = ta;
     base[n] = tb;
-    write_sizes(sizes, ta, tb, flag, counters);
+    write_sizes(sizes, ta, tb, counters[kCntTiles], flag, counters);
   }
 }
 
 size_t tile_offsets_scratch_bytes(size_t ntile) { return (ntile / kScanBlock + 1) * 2 * sizeof(uint64_t); }
 
 hipError_t launch_tile_offsets(const uint32_t *cnt, const uint32_t *rays, size_t n, uint64_t *off, uint64_t *base,
-                               const uint32_t *flag, const unsigned long long *counters, uint64_t *sizes, void *scratch,
+                               const uint32_t *flag, unsigned long long *counters, uint64_t *sizes, void *scratch,
                                hipStream_t s) {
   if (n <= kScanOneMax) {
     hipLaunchKernelGGL(k_tile_offsets_one, dim3(1), dim3(kScanOneThreads), 0, s, cnt, rays, n, off, base, flag, counters,
@@ -401,10 +410,10 @@ hipError_t launch_tile_offsets(const uint32_t *cnt, const uint32_t *rays, size_t
   }
   const size_t nb = (n + kScanBlock - 1) / kScanBlock;
   uint64_t *part = (uint64_t *)scratch;
-  hipLaunchKernelGGL(k_tile_offsets<false>, dim3((unsigned)nb), dim3(kScanThreads), 0, s, cnt, rays, n, part, off, base);
+  hipLaunchKernelGGL(k_tile_offsets<false>, dim3((unsigned)nb), dim3(kScanThreads), 0, s, cnt, rays, n, part, off, base, counters);
   hipLaunchKernelGGL(k_tile_offsets_parts, dim3(1), dim3(kScanOneThreads), 0, s, part, nb, n, off, base, flag, counters,
                      sizes);
-  hipLaunchKernelGGL(k_tile_offsets<true>, dim3((unsigned)nb), dim3(kScanThreads), 0, s, cnt, rays, n, part, off, base);
+  hipLaunchKernelGGL(k_tile_offsets<true>, dim3((unsigned)nb), dim3(kScanThreads), 0, s, cnt, rays, n, part, off, base, counters);
   return hipGetLastError();
 }
 

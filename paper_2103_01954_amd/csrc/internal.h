@@ -79,6 +79,7 @@ struct AccelView {
   int32_t combine;             // 0: sum rule, 1: sequential in primitive-id order
   int32_t item_entries;        // culling-list entries per backward work item
   float max_dist_ratio, max_inv_scale;   // over the boxes: distance / smallest half extent, 1 / half extent
+  int64_t full_tiles;          // tiles with at least one primitive
   const DevCam *cams;          // [V]
   const float4 *xf;            // [N*3]: rows of A = diag(1/s) R^T, .w = t
   const uint64_t *tile_off;    // [V*T+1]
@@ -234,6 +235,8 @@ enum : int {
   kNumCounters = 16
 };
 constexpr int kCntSlots = 64, kCntStride = 16;   // counter c of copy s at [s * kCntStride + c]
+constexpr int kCntTiles = kCntStride + kCntSizes;   // build: tiles with a primitive (in copy 1)
+constexpr int kCntHost = 2 * kCntStride + kCntSizes;   // build: the sizes for the host, if it has no pinned block (6 words, copy 2)
 __device__ __forceinline__ unsigned long long *counter_slot(unsigned long long *counters) {
   return counters + (blockIdx.x & (kCntSlots - 1)) * kCntStride;
 }
@@ -264,10 +267,10 @@ hipError_t launch_tile_fill(const AccelView &av, const int4 *rect, uint32_t *cur
                             uint32_t *tile_list, hipStream_t s);
 // offsets of the culling lists (off) and pair slots (base) of every tile from
 // its list length and rays (256, or rays[t] of a ray subset), and the build's
-// five sizes (see write_sizes) to `sizes`, device or pinned host memory
+// six sizes (see write_sizes) to `sizes`, device or pinned host memory
 size_t tile_offsets_scratch_bytes(size_t ntile);
 hipError_t launch_tile_offsets(const uint32_t *cnt, const uint32_t *rays, size_t ntile, uint64_t *off, uint64_t *base,
-                               const uint32_t *flag, const unsigned long long *counters, uint64_t *sizes, void *scratch,
+                               const uint32_t *flag, unsigned long long *counters, uint64_t *sizes, void *scratch,
                                hipStream_t s);
 // the transposed culling lists (primitive -> its entries, from the rectangles)
 // and the backward's work items, with the primitives in screen order (prim[N]);
