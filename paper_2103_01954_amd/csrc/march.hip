@@ -1968,6 +1968,20 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES))
   }
 }
 
+// Static LDS of k_bwd_items by its workgroup size: the tables' bytes, and the
+// bound that room for the dynamic part is reckoned with.
+constexpr size_t bwd_items_tables(int threads) {
+  const size_t waves = threads / kWave, ent = threads == kSparseThreads ? kSparseEntries : kItemEntries, sub = 4 * ent;
+  return 16 + kLenBuckets * 4 * (1 + 2 + 2 * waves) + waves * (64 + 4) + sub * (8 + 4) + 4 + sub / kWave * 4 + ent * (8 + 4) +
+         64;   // (alignment)
+}
+constexpr size_t bwd_items_static(int threads) {
+  return threads == kTileThreads ? 8 * 1024 : threads == kSparseThreads ? 10 * 1024 : 16 * 1024;
+}
+static_assert(bwd_items_tables(kTileThreads) <= bwd_items_static(kTileThreads) &&
+              bwd_items_tables(2 * kTileThreads) <= bwd_items_static(2 * kTileThreads) &&
+              bwd_items_tables(kSparseThreads) <= bwd_items_static(kSparseThreads), "static LDS of k_bwd_items");
+
 // The work-item kernel for 3 waves per SIMD, 2 workgroups per CU, one of 512
 // threads, one of 512 threads in slabs, or of 64 threads for sparse rays.
 enum class BwdShape { kThree, kTwo, kOne, kSlabs, kSparse };
@@ -2050,11 +2064,11 @@ hipError_t launch_march_bwd(const AccelView &av, const mvp_prims &p, int64_t n_i
   if (e != hipSuccess || p.n_prim == 0 || n_items_max == 0) return e;
   // the planar 64-bit LDS gradient, when one workgroup's copy fits a CU; its
   // padded layout unless only the packed one fits
-  const size_t kStatic = 8192;   // static LDS of a 256-thread workgroup is under 8 KB (512: under 16 KB)
+  const size_t kStatic = bwd_items_static(kTileThreads), kStaticWide = bwd_items_static(2 * kTileThreads);
   auto lds_bytes = [&](bool pad) { return (size_t)lds_map(p.M, pad).plane * 4 * sizeof(unsigned long long); };
-  const int padded = lds_bytes(true) + fade_shm + 2 * kStatic <= 160 * 1024 ? 1 : 0;
+  const int padded = lds_bytes(true) + fade_shm + kStaticWide <= 160 * 1024 ? 1 : 0;
   size_t lds = lds_bytes(padded != 0);
-  bool in_lds = g_pay && lds + fade_shm + 2 * kStatic <= 160 * 1024;
+  bool in_lds = g_pay && lds + fade_shm + kStaticWide <= 160 * 1024;
   // A larger payload (up to 45^3): slabs of as many cell layers as fit beside
   // the ordering buffer of 4096 pairs, each replaying the samples in it; every
   // pair is set up once per slab (11 of 3 layers for 32^3), but adds to the LDS.
@@ -2068,7 +2082,7 @@ hipError_t launch_march_bwd(const AccelView &av, const mvp_prims &p, int64_t n_i
   const bool sparse = av.item_entries > kItemEntries;
   if (g_pay && !in_lds && !sparse) {
     const size_t layer = (size_t)p.M * p.M * 4 * sizeof(unsigned long long);
-    const int layers = (int)((160 * 1024 - 2 * kStatic - fade_shm - 4096 * 3 - 64) / layer);
+    const int layers = (int)((160 * 1024 - kStaticWide - fade_shm - 4096 * 3 - 64) / layer);
     if (layers >= 2) {
       const int n_slab = (p.M - 2 + layers - 1) / (layers - 1);
       slab_cells = (p.M - 2 + n_slab) / n_slab;
@@ -2097,8 +2111,9 @@ hipError_t launch_march_bwd(const AccelView &av, const mvp_prims &p, int64_t n_i
   // holds keep their pairs in list order)
   uint32_t sort_cap = 0;
   if (kSortPairs) {
-    const size_t wgs = shape == BwdShape::kThree ? 3 : (shm + kStatic <= 80 * 1024 ? 2 : 1);
-    const size_t share = 160 * 1024 / wgs - (wide() ? 2 * kStatic : kStatic);
+    const size_t fixed = bwd_items_static(sparse ? kSparseThreads : wide() ? 2 * kTileThreads : kTileThreads);
+    const size_t wgs = shape == BwdShape::kThree ? 3 : (shm + fixed <= 80 * 1024 ? 2 : 1);
+    const size_t share = 160 * 1024 / wgs - fixed;
     const size_t room = share > shm ? (share - shm) / (sizeof(uint16_t) + 1) : 0;
     const size_t want = sparse ? kSparseSort : (size_t)av.item_entries * kTileThreads;
     sort_cap = (uint32_t)(std::min(room, want) / kTileThreads * kTileThreads);
