@@ -519,9 +519,9 @@ mvp_status build_accel(mvp_ctx *ctx, const mvp_prims *prims, const mvp_camera *c
   a->n_items_max = for_backward ? (int64_t)(n_tile_pairs / a->item_entries) + N : 0;
   if (for_backward) MVP_CHECK(keep.get(&a->item_lists, (size_t)a->n_items_max + 2));
   // Every ray's pairs, the entry frames and the per-entry pair lists: by the
-  // pairs kernel now, with the transposed lists beside it, or, where the march
-  // is long enough to hide those (8192 tiles of payloads of at most 8^3), with
-  // the first forward, so that their launches are off the path to it.
+  // pairs kernel, launched now or, where the forward takes long enough to hide
+  // the launch (8192 tiles of payloads of at most 8^3), with the first forward.  (The
+  // transposed lists follow the first forward or backward, see launch_lists.)
   a->po = PairsOut{a->ef, a->pr, a->ray_seg, a->ray_nj, a->ent_base, a->ent_n, a->ent_tile, a->ent_rec,
                    a->counters, !for_backward || backward_by_runs(av, prims->M)};
   // MVP_PAIRS_IN_FORWARD=1 or 0 overrides the choice (tests and tuning)

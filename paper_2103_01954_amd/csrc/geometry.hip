@@ -39,11 +39,6 @@ __global__ void k_zero_u32(uint32_t *p, size_t n) {
   size_t stride = (size_t)gridDim.x * blockDim.x;
   for (; i < n; i += stride) p[i] = 0u;
 }
-__global__ void k_zero_u64(uint64_t *p, size_t n) {
-  size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  size_t stride = (size_t)gridDim.x * blockDim.x;
-  for (; i < n; i += stride) p[i] = 0ull;
-}
 
 __global__ void k_zero_counters(unsigned long long *c, int first, int n) {
   for (int i = threadIdx.x; i < kCntSlots * n; i += blockDim.x) c[(i / n) * kCntStride + first + i % n] = 0ull;
@@ -75,11 +70,6 @@ static unsigned grid_for(size_t n, unsigned block) {
 hipError_t launch_zero_u32(uint32_t *p, size_t n, hipStream_t s) {
   if (n == 0) return hipSuccess;
   hipLaunchKernelGGL(k_zero_u32, dim3(grid_for(n, 256)), dim3(256), 0, s, p, n);
-  return hipGetLastError();
-}
-hipError_t launch_zero_u64(uint64_t *p, size_t n, hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_zero_u64, dim3(grid_for(n, 256)), dim3(256), 0, s, p, n);
   return hipGetLastError();
 }
 

@@ -42,13 +42,15 @@ struct DevCam {
 // rays touch neighbouring slots).  Ray slot r has ray_nj[r].x pairs, the q-th
 // at pr[ray_seg[r] + q * R_t], sorted by first sample and then primitive id;
 // pair p is pr[p] = (jlo, jhi, position in the tile's culling list, primitive
-// id), and ray_nj[r].y is the ray's first sample (INT_MAX if none).  The same pairs by culling-list entry, for the backward: entry g at
-// position e of tile t = ent_tile[g] lists the pairs formed with it (at most
-// one per ray of the tile), in ray order, from ent_base[g] = pair_base[t] +
-// e * R_t: the rays of wave w of the tile (ray numbers 64w .. 64w + 63) at
-// ent_rec[ent_base[g] + 64 w .. + ent_n[4g + w]).  A record is
-// (jlo | i << 24, jhi) with i the ray's number in the tile (sample indices
-// stay below 2^24).
+// id), and ray_nj[r].y is the ray's first sample (INT_MAX if none).
+// The same pairs by culling-list entry, for the backward: entry g at position e
+// of tile t = ent_tile[g] lists the pairs formed with it (at most one per ray of
+// the tile) from ent_base[g] = pair_base[t] + e * R_t, in four parts: those of
+// wave w of the pairs kernel at ent_rec[ent_base[g] + 64 w .. + ent_n[4g + w]).  A
+// wave's rays are numbers 64w .. 64w + 63 of the tile or, with PairsOut.square,
+// one 8 x 8 block of its pixels; a tile of few rays is taken by wave 0 alone.  A
+// record is (jlo | i << 24, jhi) with i the ray's number in the tile (sample
+// indices stay below 2^24).
 // Per-ray constants of the backward: Tdot, the clamp weight ((1 - T_{S-1}) /
 // sigma_S for the sum rule, 1 - T* for the sequential combine) and the
 // clamping primitive of the sequential combine (-1: none).
@@ -88,7 +90,7 @@ struct AccelView {
   const uint32_t *prim_entries;    // [n_tile_pairs]
   const uint64_t *item_off;        // [N+1], over the primitives in the order item_prim
   const uint32_t *item_prim;       // [N] the backward's order of the primitives
-  uint32_t *item_lists;            // [2 + work items] scratch of the backward (k_item_split)
+  uint32_t *item_lists;            // [2 + work items] scratch of the backward: two counts and lists (k_item_split)
   const float4 *ef;            // [3 n_tile_pairs]
   const uint64_t *pair_base;   // [V*T+1]
   const uint64_t *ray_seg;     // [R]
@@ -248,7 +250,6 @@ inline uint64_t sum_counter(const uint64_t *copies, int c) {   // of a host copy
 
 // ---- launchers (return the first HIP error) --------------------------------
 hipError_t launch_zero_u32(uint32_t *p, size_t n, hipStream_t s);
-hipError_t launch_zero_u64(uint64_t *p, size_t n, hipStream_t s);
 // clear counters first .. first + n - 1 in every slot
 hipError_t launch_zero_counters(unsigned long long *counters, int first, int n, hipStream_t s);
 // start of a build: clear n_tiles words of tile counters and the counters, and

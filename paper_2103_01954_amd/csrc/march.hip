@@ -24,17 +24,17 @@
 // and for the sequential combine Tdot = -g . c_k*S, the primitives before k*
 // at S take the j < S formulas, dL/dc_k*S = (1 - T*) g with T* the opacity
 // just before k*, and dL/dsigma_k*S = 0.
-// The pairs are replayed by work items, each up to 32 or 64 culling-list
-// entries (screen tile, primitive) of one primitive: channel adjoints go to
-// the 8 voxel corners with the trilinear weights, accumulated in registers
-// over a run of samples in one cell and then in an LDS copy of the
-// primitive's gradient held in 64-bit fixed point (LDS 64-bit integer atomic
-// adds run about 25 times faster than FP32 ones on gfx950, and integer sums do
-// not depend on the order of the additions), which is added to device memory
-// once per item; the pose gradient (through y = A (o + t d - pos)) is reduced
-// over the workgroup.  The fixed-point scale of an item is chosen from a bound
-// on what any one of its pairs can add to one gradient value: every single
-// addend then fits 32 bits and no 64-bit sum can overflow.
+// The pairs are replayed by work items, each 16 to 128 culling-list entries
+// (screen tile, primitive) of one primitive: channel adjoints go to the 8
+// voxel corners with the trilinear weights, formed over a run of samples in one
+// cell and then added to an LDS copy of the primitive's gradient (or of a slab
+// of it) held in 64-bit fixed point (LDS 64-bit integer atomic adds run about 25
+// times faster than FP32 ones on gfx950, and integer sums do not depend on the
+// order of the additions), which is added to device memory once per item; the
+// pose gradient (through y = A (o + t d - pos)) is reduced over the workgroup.
+// The fixed-point scale of an item is chosen from a bound on what any one of its
+// pairs can add to one gradient value: every single addend then fits 32 bits (50
+// where it is converted in two parts) and no 64-bit sum can overflow.
 //
 // Built with -ffp-contract=off; fused multiply-adds are written explicitly.
 #include <hip/hip_runtime.h>
@@ -49,14 +49,13 @@
 
 namespace mvp {
 
-// Largest number of culling-list entries per backward work item (the build
-// picks the number per structure, see backward_item_entries), the shape of those
-// of sparse rays (that many entries for a workgroup of 64), and how the
-// pairs of an item too large for the ordering buffer (below) are dealt to its
-// threads.
+// Largest number of culling-list entries per backward work item of 256 or 512
+// threads (the build picks the number per structure, see backward_item_entries),
+// the shape of those of sparse rays (64 threads), and how the pairs of an item
+// too large for the ordering buffer (below) are dealt to its threads.
 constexpr int kItemEntries = 64;
 constexpr int kSparseMaxM = 10;   // largest payload for it
-constexpr int kSparseThreads = kWave, kSparseEntries = 128, kSparseSort = 1024;   // pairs it orders
+constexpr int kSparseThreads = kWave, kSparseEntries = 128, kSparseSort = 1024;   // (the last: pairs it orders)
 constexpr bool kChunkedPairs = true;
 // Lanes accumulate in cell coordinates mirrored by (lane mod 8), so lanes that
 // flush the same cell add to different corners in each instruction.
@@ -522,7 +521,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
     bool act = n > 0;
     int e0 = 0;                // pairs before e0 have ended before the window
     int base = 0, ready = 0;   // pairs [base, ready) are staged; slot `ready` of the ring is the sentinel
-    // stage pairs [ready, ready + kWin) of the ray: one per lane
+    // stage pairs [ready, ready + kBatch) of the ray: kBatch / kWin per lane
     auto stage = [&]() {
       constexpr int kB = kBatch / kWin;
       const int i0 = ready + w;
@@ -1586,7 +1585,9 @@ __device__ __forceinline__ float fixed_scale(float bound, uint32_t total) {
 // the latter go to device memory where they would be more than kSlabsAtLeast slabs
 // (about eight for each CU; fewer are hidden better than another kernel's
 // latency).  64 x 32^3, 1000 rays: backward of 300 us, 3000 all in slabs; 4000 x
-// 32^3 at 64 x 64: 1.5 against 6.4 ms.
+// 32^3 at 64 x 64: 1.5 against 6.4 ms.  Both ways take as long at 25 pairs an item
+// with 2 slabs (17^3, 18^3), 30 with 3 (20^3), 36 to 50 with 4 (24^3), 55 to 85 with
+// 11 (32^3) and 60 to 140 with 39 (40^3): few = 20 + 4 for each slab, up to 100.
 constexpr uint32_t kSlabsAtLeast = 2048;
 __global__ __launch_bounds__(kWave) void k_item_split(AccelView av, uint32_t few, uint32_t n_list) {
   const uint32_t it = blockIdx.x * (uint32_t)kWave + threadIdx.x;
@@ -1629,8 +1630,8 @@ __global__ __launch_bounds__(kWave) void k_item_split(AccelView av, uint32_t few
 // Length classes for ordering pairs: exact below 32 samples, then 4 wide.
 __device__ __forceinline__ int len_bucket(int n) { return n < 32 ? n : min(kLenBuckets - 1, 32 + ((n - 32) >> 2)); }
 
-// Backward, one workgroup per work item: up to kItemEntries culling-list
-// entries (tile, primitive k) of one primitive.  The pairs of those entries
+// Backward, one workgroup per work item: up to kItemEntries (for sparse rays
+// kSparseEntries) culling-list entries (tile, primitive k) of one primitive.  The pairs of those entries
 // (at most one per ray of each tile) are spread over the workgroup's threads;
 // the payload gradient of k is accumulated in LDS (LDS_ACC, 64-bit fixed point
 // with the item's scale) and added to device memory once per item, the pose
@@ -2012,12 +2013,12 @@ static BwdItemsFn bwd_items_fn(bool bf16, bool lds, bool fade, bool runs, BwdSha
 // - at least 3 samples per voxel cell across the smallest box (7 for 4096 x 8^3
 //   at 1/512: 1.6 times as fast as the sample loop; 10 for 512 x 16^3: 2.4
 //   times; 2.7 for 32768 x 16^3 at 1/1024: equal);
-// - no box smaller than 1/90 of its distance.  The sample loop's sums of the
-//   rotation and scale gradients run over camera distances, and their FP32
-//   rounding grows with this ratio (about 1.0e-5 of the gradient at 86, 2.2e-5 at
-//   210); the closed form has less of it (1e-6), but past this line the change
-//   from the one to the other would be larger than a gradient may move between
-//   versions (2e-5).
+// - no box smaller than 1/90 of its distance.  This line is for continuity, not
+//   for speed or accuracy: the sample loop's sums of the rotation and scale
+//   gradients run over camera distances, and their FP32 rounding grows with this
+//   ratio (about 1.0e-5 of the gradient at 86, 2.2e-5 at 210) where the closed
+//   form's does not (1e-6), so far from the camera its results would differ from
+//   the sample loop's, which they have always had, by more than 2e-5.
 bool backward_by_runs(const AccelView &av, int M) {
   const float cell = 2.0f / (av.max_inv_scale * (float)(M - 1));
   return cell >= 3.0f * av.step && av.max_dist_ratio <= 90.0f;
@@ -2073,7 +2074,7 @@ hipError_t launch_march_bwd(const AccelView &av, const mvp_prims &p, int64_t n_i
   // the ordering buffer of 4096 pairs, each replaying the samples in it; every
   // pair is set up once per slab (11 of 3 layers for 32^3), but adds to the LDS.
   // Device atomics in their place, 32 per cell run, ran at 46 G/s: 64 x 32^3 at
-  // 667 x 1024 48.4 ms against 3.6.
+  // 667 x 1024 48.4 ms against 3.4; items of few pairs are left to them (k_item_split).
   int slab_cells = 0;
   // The items' length was chosen at the build, for its payload size and way
   // through a pair; this call's payload may be of another size.  Items of more
@@ -2176,7 +2177,8 @@ hipError_t launch_march_bwd(const AccelView &av, const mvp_prims &p, int64_t n_i
 // backward_by_runs), and the largest case is fastest at 64 (32768 of 16^3: 28.3
 // ms with 32, 27.4 with 64).  Payloads taken in slabs have items of at most 4096
 // pairs, the ordering buffer's size beside a slab (64 of 32^3: 3.6 ms with 16
-// entries, 4.8 with 8 or 32).
+// entries, 4.8 with 8 or 32).  Larger ones, in device memory, take 16 too (8 x 64^3 at
+// 667 x 1024: 24 ms, 59 with 64 and the sample loop).
 int backward_item_entries(const AccelView &av, int M, uint64_t n_entries, uint64_t n_slots) {
   if (M > 16) return 16;
   if (!backward_by_runs(av, M)) return M <= 8 ? 32 : kItemEntries;
