@@ -43,6 +43,7 @@
 #include <algorithm>
 #include <type_traits>
 #include <climits>
+#include <cmath>
 
 #include "internal.h"
 #include "pairs.h"
@@ -663,7 +664,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
             T = Tn;
             if (!over) {
               act = ws == kWin;
-            } else if (!SEQ || !(tw > 1.0f)) {   // (NaN: under either rule the whole sample's)
+            } else if (!SEQ) {
               const float wgt = (1.0f - T) / ss;
               I0 = fmaf(s0, wgt, I0);
               I1 = fmaf(s1, wgt, I1);
@@ -674,10 +675,11 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
             } else {   // every lane of the ray takes the same walk
               RayState st{T, I0, I1, I2, -1.0f};
               const bool stop = seq_sample<BF16, FADE>(av, lb, pay, s_fade, seg, stride, n, d, J + ws, st);
+              const bool nan = tw != tw;   // a NaN density: so is the colour, as under the sum rule
               T = st.T;
-              I0 = st.I0;
-              I1 = st.I1;
-              I2 = st.I2;
+              I0 = nan ? tw : st.I0;
+              I1 = nan ? tw : st.I1;
+              I2 = nan ? tw : st.I2;
               if (stop) {
                 t_prev = st.t_prev;
                 act = false;
@@ -1121,12 +1123,19 @@ __device__ __forceinline__ void clip_to_slab(const Slab &sl, float a, float b, f
   hi = x;
 }
 
+// How a pair is replayed: sample by sample, or by runs in closed form, whose
+// samples are equidistant if dt is a power of two.  Otherwise their times fl(j dt)
+// are off by a rounding each, which the sample loop takes as it comes and the closed
+// form to first order (a payload gradient of 46^3 at 574 samples per unit: 1.0e-6
+// from that in 64 bits, 1.1e-5 if they are left out; 1.1e-6 by the loop).
+enum class Replay { kLoop, kRuns, kRounded };
+
 // Replay one (ray, primitive k) pair backward: channel adjoints to the 8
 // voxel corners (registers over a run of samples in one cell, then gdst:
 // the LDS copy of k's gradient or device memory) and the pair's pose sums
 // added to P (12 values, see the end and pose_from_sums).
 //
-// RUNS: a run is taken in closed form, not sample by sample.  g . c and the
+// Closed form (R): a run is not taken sample by sample.  g . c and the
 // opacity are cubics in n (LineFn), an ordinary sample's adjoints are dt times
 // them (plus a constant), so their moments sum_n n^k (.) over the run follow
 // from the power sums of n, and every sum over the run's samples (corner
@@ -1136,7 +1145,7 @@ __device__ __forceinline__ void clip_to_slab(const Slab &sl, float a, float b, f
 // 8^3, four 1024^2 views (5 samples per run): 6.5 -> 4.2 ms; 512 x 16^3 at
 // 667 x 1024: 4.4 -> 1.9 ms.  At 2 samples per run the two are equal (32768 x
 // 16^3 at 2 x 2048^2: 26.8 and 27.0 ms): see backward_by_runs.
-template <bool BF16, bool LDS_ACC, bool FADE, bool RUNS, bool SLABS, bool PREFETCH, bool WIDE, typename GAcc>
+template <bool BF16, bool LDS_ACC, bool FADE, Replay R, bool SLABS, bool PREFETCH, bool WIDE, typename GAcc>
 __device__ __forceinline__ void bwd_pair(const AccelView &av, const char *__restrict__ payk,
                                          const mvp_ray_aux *__restrict__ aux, const float4 *__restrict__ grad_rgba,
                                          const RayConst *__restrict__ rc, const uint2 rec, uint64_t gent, int tile,
@@ -1205,7 +1214,7 @@ __device__ __forceinline__ void bwd_pair(const AccelView &av, const char *__rest
   // free of the cancellation of camera distances (60 box sizes on the 4096 x 8^3
   // scene).
   const float tref = 0.5f * (float)(jr.x + jh) * dt;
-  if constexpr (RUNS) {
+  if constexpr (R != Replay::kLoop) {
     // offsets per sample, signed by direction and (p, q, r) mirrored; samples per
     // unit of offset
     const float s0 = B.x * hM * dt, s1 = B.y * hM * dt, s2 = B.z * hM * dt;
@@ -1234,7 +1243,7 @@ __device__ __forceinline__ void bwd_pair(const AccelView &av, const char *__rest
       const float ex = fminf(fmaxf(fminf(fminf(e0, e1), e2) - jslack, 0.0f), (float)(kRunMax - 1));
       const int jl = min(j + (int)ex, jh);
       const bool sp = clamped && jl == ax.j_end && (!seq || k >= rcv.kstar);   // it is the clamping sample
-      const int L = jl - j + (sp ? 0 : 1);         // ordinary samples of the run
+      const int j0 = j, L = jl - j + (sp ? 0 : 1);   // first and number of the run's ordinary samples
       const float jm = 0.5f * (float)(j + j + L - 1);   // their middle
       const float tm = jm * dt;
       // offsets from the cell's own corner ((M-1)/2 - index is exact): rounded once,
@@ -1297,8 +1306,42 @@ __device__ __forceinline__ void bwd_pair(const AccelView &av, const char *__rest
         V2 = fmaf(S4, fg.c2, S2 * h0);
         V3 = fmaf(S6, fg.c3, S4 * fg.c1);
       }
+      if constexpr (R == Replay::kRounded) {
+        // A sample at n + e / dt in place of n adds e f'(n) to a moment dt sum f(n) of
+        // the monomials up to n^3 times a cubic: the sums of e n^k up to n^5 take all of
+        // it to first order (e / dt is below 1e-3).
+        float E0 = 0.f, E1 = 0.f, E2 = 0.f, E3 = 0.f, E4 = 0.f, E5 = 0.f;
+        for (int i = 0; i < L; ++i) {
+          const float n = (float)(j0 + i) - jm;
+          float e = fmaf(-n, dt, (float)(j0 + i) * dt - tm);
+          E0 += e;
+          e *= n;
+          E1 += e;
+          e *= n;
+          E2 += e;
+          e *= n;
+          E3 += e;
+          e *= n;
+          E4 += e;
+          E5 = fmaf(e, n, E5);
+        }
+        E1 *= 2.0f;
+        E2 *= 3.0f;
+        E3 *= 4.0f;
+        E4 *= 5.0f;
+        E5 *= 6.0f;
+        auto shift = [&](float c0, float c1, float c2, float c3, float &M0, float &M1, float &M2, float &M3) {
+          M0 = fmaf(c1, E0, fmaf(c2, E1, fmaf(c3, E2, M0)));
+          M1 = fmaf(c0, E0, fmaf(c1, E1, fmaf(c2, E2, fmaf(c3, E3, M1))));
+          M2 = fmaf(c0, E1, fmaf(c1, E2, fmaf(c2, E3, fmaf(c3, E4, M2))));
+          M3 = fmaf(c0, E2, fmaf(c1, E3, fmaf(c2, E4, fmaf(c3, E5, M3))));
+        };
+        shift(fs.c0, fs.c1, fs.c2, fs.c3, W0, W1, W2, W3);
+        shift(tdot + fg.c0, fg.c1, fg.c2, fg.c3, V0, V1, V2, V3);
+      }
       if (sp) {
-        const float n = (float)jl - jm;
+        float n = (float)jl - jm;
+        if constexpr (R == Replay::kRounded) n = fmaf(fmaf(-n, dt, (float)jl * dt - tm), __builtin_amdgcn_rcpf(dt), n);
         const float gc = fmaf(n, fmaf(n, fmaf(n, fg.c3, fg.c2), fg.c1), fg.c0);
         const float sg = fmaf(n, fmaf(n, fmaf(n, fs.c3, fs.c2), fs.c1), fs.c0);
         float a3 = seq ? 0.f : wsig * (gc + tdot);
@@ -1490,7 +1533,7 @@ __device__ __forceinline__ void bwd_pair(const AccelView &av, const char *__rest
   const float G[3] = {hMx * G0, hMy * G1, hMz * G2}, H[3] = {hMx * H0, hMy * H1, hMz * H2};
 #pragma unroll
   for (int mm = 0; mm < 3; ++mm) {
-    const float w = RUNS ? fmaf(tref, d[mm], cam.o[mm] - t[mm]) : cam.o[mm];
+    const float w = R != Replay::kLoop ? fmaf(tref, d[mm], cam.o[mm] - t[mm]) : cam.o[mm];
 #pragma unroll
     for (int i = 0; i < 3; ++i) P[3 + 3 * mm + i] = fmaf(w, G[i], fmaf(d[mm], H[i], P[3 + 3 * mm + i]));
   }
@@ -1500,10 +1543,10 @@ __device__ __forceinline__ void bwd_pair(const AccelView &av, const char *__rest
 
 // Output i (0-2 dL/dt, 3-11 dL/dR row-major, 12-14 dL/ds) of primitive k's
 // pose gradient from the sums of its pairs (bwd_pair): SG = sum G and
-// S[m][i] = sum (x - t)_m dL/dy_i (RUNS) or sum x_m dL/dy_i.  With
+// S[m][i] = sum (x - t)_m dL/dy_i (CENTRED, the closed form) or sum x_m dL/dy_i.  With
 // P_mi = S_mi, or S_mi - t_m SG_i: dL/dt_m = -sum_i A_im SG_i,
 // dL/dR_mi = P_mi / s_i, dL/ds_i = -sum_m R_mi P_mi / s_i^2.
-template <bool RUNS>
+template <bool CENTRED>
 __device__ __forceinline__ float pose_from_sums(const AccelView &av, const float *__restrict__ rot,
                                                 const float *__restrict__ scale, int k, const float *sums,
                                                 int i) {
@@ -1513,7 +1556,7 @@ __device__ __forceinline__ float pose_from_sums(const AccelView &av, const float
     const float4 row = av.xf[3 * (size_t)k + r];
     Am[3 * r] = row.x; Am[3 * r + 1] = row.y; Am[3 * r + 2] = row.z; t[r] = row.w;
   }
-  auto rel = [&](int m, int c) { return RUNS ? sums[3 + 3 * m + c] : sums[3 + 3 * m + c] - t[m] * sums[c]; };
+  auto rel = [&](int m, int c) { return CENTRED ? sums[3 + 3 * m + c] : sums[3 + 3 * m + c] - t[m] * sums[c]; };
   if (i < 3) return -fmaf(Am[6 + i], sums[2], fmaf(Am[3 + i], sums[1], Am[i] * sums[0]));
   if (i < 12) return rel((i - 3) / 3, (i - 3) % 3) / scale[3 * (size_t)k + (i - 3) % 3];
   const int c = i - 12;
@@ -1642,7 +1685,7 @@ __device__ __forceinline__ int len_bucket(int n) { return n < 32 ? n : min(kLenB
 // LDS gradient leaves room for that many workgroups per CU.  THREADS is the
 // workgroup size: 512 when the LDS gradient leaves room for only one
 // workgroup per CU, so that the CU still runs two waves per SIMD.
-template <bool BF16, bool LDS_ACC, bool FADE, bool RUNS, int WAVES, int THREADS, bool SLABS = false>
+template <bool BF16, bool LDS_ACC, bool FADE, Replay R, int WAVES, int THREADS, bool SLABS = false>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES))) void k_bwd_items(
     AccelView av, const float *__restrict__ rot, const float *__restrict__ scale, const void *__restrict__ pay,
     const mvp_ray_aux *__restrict__ aux, const float4 *__restrict__ grad_rgba, const RayConst *__restrict__ rc,
@@ -1869,7 +1912,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES))
           if (s_pre[mid] <= i) q = mid; else hi = mid - 1;
         }
         const uint2 rec = av.ent_rec[s_start[q] + (i - s_pre[q])];
-        bwd_pair<BF16, LDS_ACC, FADE, RUNS, SLABS, WAVES == 1, kWide>(av, payk, aux, grad_rgba, rc, rec, s_gent[q >> 2], s_tile[q >> 2], k, t, slab, gdst,
+        bwd_pair<BF16, LDS_ACC, FADE, R, SLABS, WAVES == 1, kWide>(av, payk, aux, grad_rgba, rc, rec, s_gent[q >> 2], s_tile[q >> 2], k, t, slab, gdst,
                                       lm, fxs, s_fade, pose, P, n_run);
         ++n_rep;
       }
@@ -1910,7 +1953,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES))
       for (uint32_t i = i0, q = q0; i < iend; i += stride) {
         while (s_pre[q + 1] <= i) ++q;
         const uint2 rec = av.ent_rec[s_start[q] + (i - s_pre[q])];
-        bwd_pair<BF16, LDS_ACC, FADE, RUNS, SLABS, WAVES == 1, kWide>(av, payk, aux, grad_rgba, rc, rec, s_gent[q >> 2], s_tile[q >> 2], k, t, slab, gdst,
+        bwd_pair<BF16, LDS_ACC, FADE, R, SLABS, WAVES == 1, kWide>(av, payk, aux, grad_rgba, rc, rec, s_gent[q >> 2], s_tile[q >> 2], k, t, slab, gdst,
                                       lm, fxs, s_fade, pose, P, n_run);
         ++n_rep;
       }
@@ -1934,7 +1977,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES))
     __syncthreads();
     if (pose && threadIdx.x < 15 && total > 0) {
       const int i = threadIdx.x;
-      const float x = pose_from_sums<RUNS>(av, rot, scale, k, s_pose[0], i);
+      const float x = pose_from_sums<R != Replay::kLoop>(av, rot, scale, k, s_pose[0], i);
       if (i < 3) {
         if (out.pos) unsafeAtomicAdd(out.pos + 3 * (size_t)k + i, x);
       } else if (i < 12) {
@@ -1988,7 +2031,7 @@ static_assert(bwd_items_tables(kTileThreads) <= bwd_items_static(kTileThreads) &
 enum class BwdShape { kThree, kTwo, kOne, kSlabs, kSparse };
 typedef void (*BwdItemsFn)(AccelView, const float *, const float *, const void *, const mvp_ray_aux *, const float4 *,
                            const RayConst *, const RayBound *, BwdOut, uint32_t, int, int, uint32_t, unsigned long long *);
-template <bool B, bool L, bool F, bool R>
+template <bool B, bool L, bool F, Replay R>
 static BwdItemsFn bwd_items_fn(BwdShape shape) {
   if (shape == BwdShape::kThree) return k_bwd_items<B, L, F, R, 3, kTileThreads>;
   if (shape == BwdShape::kSparse) return k_bwd_items<B, L, F, R, 1, kSparseThreads>;
@@ -1999,14 +2042,17 @@ static BwdItemsFn bwd_items_fn(BwdShape shape) {
   }
   return nullptr;   // without the LDS copy three workgroups fit
 }
-template <bool B, bool L>
-static BwdItemsFn bwd_items_fn(bool fade, bool runs, BwdShape shape) {
-  return fade ? (runs ? bwd_items_fn<B, L, true, true>(shape) : bwd_items_fn<B, L, true, false>(shape))
-              : (runs ? bwd_items_fn<B, L, false, true>(shape) : bwd_items_fn<B, L, false, false>(shape));
+template <bool B, bool L, bool F>
+static BwdItemsFn bwd_items_fn(Replay r, BwdShape shape) {
+  return r == Replay::kRuns ? bwd_items_fn<B, L, F, Replay::kRuns>(shape)
+         : r == Replay::kRounded ? bwd_items_fn<B, L, F, Replay::kRounded>(shape) : bwd_items_fn<B, L, F, Replay::kLoop>(shape);
 }
-static BwdItemsFn bwd_items_fn(bool bf16, bool lds, bool fade, bool runs, BwdShape shape) {
-  return bf16 ? (lds ? bwd_items_fn<true, true>(fade, runs, shape) : bwd_items_fn<true, false>(fade, runs, shape))
-              : (lds ? bwd_items_fn<false, true>(fade, runs, shape) : bwd_items_fn<false, false>(fade, runs, shape));
+static BwdItemsFn bwd_items_fn(bool bf16, bool lds, bool fade, Replay r, BwdShape shape) {
+  if (bf16)
+    return lds ? (fade ? bwd_items_fn<true, true, true>(r, shape) : bwd_items_fn<true, true, false>(r, shape))
+               : (fade ? bwd_items_fn<true, false, true>(r, shape) : bwd_items_fn<true, false, false>(r, shape));
+  return lds ? (fade ? bwd_items_fn<false, true, true>(r, shape) : bwd_items_fn<false, true, false>(r, shape))
+             : (fade ? bwd_items_fn<false, false, true>(r, shape) : bwd_items_fn<false, false, false>(r, shape));
 }
 
 // Whether the backward takes cell runs in closed form (bwd_pair).  Two lines:
@@ -2120,7 +2166,9 @@ hipError_t launch_march_bwd(const AccelView &av, const mvp_prims &p, int64_t n_i
     sort_cap = (uint32_t)(std::min(room, want) / kTileThreads * kTileThreads);
     shm += (size_t)sort_cap * (sizeof(uint16_t) + 1);
   }
-  const bool runs = backward_by_runs(av, p.M);
+  int exponent;
+  const Replay runs = !backward_by_runs(av, p.M) ? Replay::kLoop
+                      : std::frexp(av.step, &exponent) == 0.5f ? Replay::kRuns : Replay::kRounded;
   BwdItemsFn fn = bwd_items_fn(bf16, in_lds, fade, runs, shape);
   if (shm > 64 * 1024) {
     // allow more than the default dynamic LDS per workgroup (gfx950 has 160 KB)
