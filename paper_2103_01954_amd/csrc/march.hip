@@ -432,7 +432,9 @@ __device__ __forceinline__ bool march_tile(const AccelView &av, int64_t u, int *
 }
 
 // 4 waves per SIMD: 5 spill and crowd the L1 (32768 x 16^3: 23 against 16 ms).
-template <bool BF16, bool FADE, bool SEQ, bool BIG>
+// GENERAL: payloads above 256^3 (voxel_index) and nearly empty pictures (skip), kept
+// out of the kernel for the others, which they cost up to 1%.
+template <bool BF16, bool FADE, bool SEQ, bool GENERAL>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void k_march_fwd(
     AccelView av, const char *__restrict__ pay, const float *__restrict__ bg, float4 *__restrict__ rgba,
     mvp_ray_aux *__restrict__ aux, unsigned long long *__restrict__ counters, int64_t n_units, int skip) {
@@ -458,7 +460,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
   // most one per lane, are looked at together, and those in empty tiles written eight
   // at a time.
   uint64_t full = ~0ull;
-  if (skip) {
+  if (GENERAL && skip) {
     auto unit_tile = [&](int i, int *tile, int *sub) {   // unit i of the wave: 0 no unit, 1 in an empty tile, 2 in another
       const int64_t u = blockIdx.x + (int64_t)i * gridDim.x;
       if (u >= n_units || !march_tile(av, u, tile, sub)) return 0;
@@ -481,7 +483,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
     }
   }
   for (int64_t u = blockIdx.x; u < n_units; u += gridDim.x) {
-    if (skip) {
+    if (GENERAL && skip) {
       const bool take = full & 1;
       full >>= 1;
       if (!take) continue;
@@ -586,7 +588,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
             c.f[0] = u0 - q0;
             c.f[1] = u1 - q1;
             c.f[2] = u2 - q2;
-            c.idx = voxel_index<BIG>(q0, q1, q2, M, Mf);
+            c.idx = voxel_index<GENERAL>(q0, q1, q2, M, Mf);
             float4 vx[8];
             corners_at<BF16>((const char *)(pp[at][rl] + (uint64_t)(uint32_t)c.idx * kVox), row, slice, vx);
             if (FADE) {
@@ -759,14 +761,14 @@ hipError_t launch_march_fwd(const AccelView &av, const mvp_prims &p, const float
   const int skip = per > 1 && (units + grid - 1) / grid <= kWave ? 1 : 0;
   const bool fade = av.fade_alpha > 0.f;
   const size_t shm = fade ? (size_t)av.M * sizeof(float) : 0;
-  const bool big = av.M > kFloatIndexM;
-#define MVP_FWD(B, F, S, I)                                                                               \
-  hipLaunchKernelGGL((k_march_fwd<B, F, S, I>), dim3(grid), dim3(kWave), shm, s, av,                    \
+  const bool general = skip || av.M > kFloatIndexM;
+#define MVP_FWD(B, F, S, G)                                                                               \
+  hipLaunchKernelGGL((k_march_fwd<B, F, S, G>), dim3(grid), dim3(kWave), shm, s, av,                    \
                      (const char *)p.payload, bg, (float4 *)rgba, aux, counters, units, skip)
 #define MVP_FWD_S(B, F)                                                               \
   do {                                                                                \
-    if (av.combine) { if (big) MVP_FWD(B, F, true, true); else MVP_FWD(B, F, true, false); }   \
-    else { if (big) MVP_FWD(B, F, false, true); else MVP_FWD(B, F, false, false); }   \
+    if (av.combine) { if (general) MVP_FWD(B, F, true, true); else MVP_FWD(B, F, true, false); }   \
+    else { if (general) MVP_FWD(B, F, false, true); else MVP_FWD(B, F, false, false); }   \
   } while (0)
   if (p.payload_dtype == MVP_BF16) {
     if (fade) MVP_FWD_S(true, true); else MVP_FWD_S(true, false);
