@@ -281,9 +281,9 @@ mvp_status mvp_debug_hits(mvp_ctx *ctx, const mvp_accel *accel, const mvp_prims 
 
 /* Kernel timing for benchmarks: from mvp_timing_start on, every forward
  * (MVP_KERNEL_FWD_MARCH: the forward march kernel) and backward
- * (MVP_KERNEL_BWD_MARCH: the per-pair backward kernel, without the per-ray
- * constants kernel before it) records a pair of HIP events around that kernel
- * on the stream it is launched on, for the first `capacity` launches of each.
+ * (MVP_KERNEL_BWD_MARCH: the per-pair backward kernel, with the split of its
+ * work items where it has one, without the per-ray constants kernel before it)
+ * records a pair of HIP events around them on the stream they are launched on, for the first `capacity` launches of each.
  * mvp_timing_read BLOCKS until the recorded launches have finished and writes
  * their durations in milliseconds to the HOST array ms [capacity], launch
  * order, and their number to *n.  mvp_timing_stop ends recording and frees
