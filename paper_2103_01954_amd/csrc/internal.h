@@ -238,6 +238,7 @@ enum : int {
 };
 constexpr int kCntSlots = 64, kCntStride = 16;   // counter c of copy s at [s * kCntStride + c]
 constexpr int kCntTiles = kCntStride + kCntSizes;   // build: tiles with a primitive (in copy 1)
+constexpr int kCntOdd = kCntStride + kCntPayMax;       // backward: not 0 if a payload value or a ray's bound is not finite (copy 1)
 constexpr int kCntHost = 2 * kCntStride + kCntSizes;   // build: the sizes for the host, if it has no pinned block (6 words, copy 2)
 __device__ __forceinline__ unsigned long long *counter_slot(unsigned long long *counters) {
   return counters + (blockIdx.x & (kCntSlots - 1)) * kCntStride;

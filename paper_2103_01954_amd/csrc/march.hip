@@ -814,8 +814,8 @@ __global__ __launch_bounds__(256) void k_bwd_rays(AccelView av, const void *__re
                                                   const float4 *__restrict__ grad_rgba,
                                                   const float *__restrict__ bg, const float4 *__restrict__ rgba,
                                                   RayConst *__restrict__ rc, RayBound *__restrict__ rbd,
-                                                  const uint32_t *__restrict__ pmax, float *__restrict__ g_bg,
-                                                  size_t R) {
+                                                  const uint32_t *__restrict__ pmax, uint32_t *__restrict__ odd,
+                                                  float *__restrict__ g_bg, size_t R) {
   extern __shared__ float s_fade[];
   __shared__ uint32_t s_clamped[kBwdRaysPerBlock];
   __shared__ int s_nc;
@@ -835,7 +835,9 @@ __global__ __launch_bounds__(256) void k_bwd_rays(AccelView av, const void *__re
     rc[r] = RayConst{tdot, wsig, kstar, 0};
     const float g1 = fabsf(g.x) + fabsf(g.y) + fabsf(g.z);
     const float gi = fmaxf(fabsf(g.x), fmaxf(fabsf(g.y), fabsf(g.z)));
-    rbd[r] = RayBound{av.step * (fabsf(tdot) + g1 * cmax + smax * gi), clamped ? gi : 0.f};
+    const RayBound b{av.step * (fabsf(tdot) + g1 * cmax + smax * gi), clamped ? gi : 0.f};
+    rbd[r] = b;
+    if (!(b.per_sample <= 1e30f && b.clamp <= 1e30f)) atomicOr(odd, 1u);   // times 2^24 samples it may overflow
   };
   for (int o = 0; o < kBwdRaysPerBlock; o += 256) {
     const size_t r = base + o + threadIdx.x;
@@ -922,16 +924,19 @@ __global__ __launch_bounds__(256) void k_bwd_rays(AccelView av, const void *__re
 
 // Largest colour and opacity magnitudes of the payload, as float bits in
 // pmax[0] and pmax[1] (which start at zero; non-negative floats order like
-// their bit patterns).
+// their bit patterns).  A value that is not finite raises *odd.
 template <bool BF16>
 __global__ __launch_bounds__(256) void k_payload_bound(const void *__restrict__ pay, size_t n_vox,
-                                                       uint32_t *__restrict__ pmax) {
+                                                       uint32_t *__restrict__ pmax, uint32_t *__restrict__ odd) {
   float c = 0.f, sg = 0.f;
+  bool finite = true;
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_vox; i += (size_t)gridDim.x * blockDim.x) {
     const float4 v = Voxels<BF16>::load(pay, i);
     c = fmaxf(c, fmaxf(fabsf(v.x), fmaxf(fabsf(v.y), fabsf(v.z))));
     sg = fmaxf(sg, fabsf(v.w));
+    finite = finite && fabsf(v.x) + fabsf(v.y) + fabsf(v.z) + fabsf(v.w) < INFINITY;
   }
+  if (__ballot(!finite) && (threadIdx.x & (kWave - 1)) == 0) atomicOr(odd, 1u);
 #pragma unroll
   for (int d = kWave / 2; d > 0; d >>= 1) {
     c = fmaxf(c, __shfl_xor(c, d, kWave));
@@ -1735,16 +1740,24 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES))
     fill_fade(s_fade, M, av.fade_alpha, av.fade_beta);
     __syncthreads();
   }
-  // n_list > 0: the items of k_item_split's lists (of at most n_list items)
+  // A payload taken in slabs (slab_cells > 0; !LDS_ACC is the kernel beside them that
+  // goes to device memory).  n_list > 0: the items of k_item_split's lists (of at
+  // most n_list items).  Values that fixed point cannot hold (*odd: infinities, NaN,
+  // bounds that overflow) leave every item to device memory.
   uint32_t n_many = 0, n_few = 0;
-  if ((SLABS || !LDS_ACC) && n_list) {
-    n_many = av.item_lists[0];
-    n_few = av.item_lists[1];
-    const uint32_t slabs = (uint32_t)((M - 2 + slab_cells) / slab_cells);
-    if (((uint64_t)n_few * slabs <= kSlabsAtLeast) != SLABS) n_few = 0;   // they are the other kernel's
-    if (!SLABS) n_many = 0;
+  bool listed = false;
+  if (SLABS || (!LDS_ACC && slab_cells > 0)) {
+    const bool odd = *(const uint32_t *)(counters + kCntOdd) != 0u;
+    if (odd ? SLABS : !SLABS && n_list == 0) return;
+    listed = n_list != 0 && !odd;
+    if (listed) {
+      n_many = av.item_lists[0];
+      n_few = av.item_lists[1];
+      const uint32_t slabs = (uint32_t)((M - 2 + slab_cells) / slab_cells);
+      if (((uint64_t)n_few * slabs <= kSlabsAtLeast) != SLABS) n_few = 0;   // they are the other kernel's
+      if (!SLABS) n_many = 0;
+    }
   }
-  const bool listed = (SLABS || !LDS_ACC) && n_list;
   const uint64_t n_items = (listed ? (uint64_t)n_many + n_few : av.item_off[av.N]) * n_slab;
   for (uint64_t is = blockIdx.x; is < n_items; is += gridDim.x) {
     uint64_t it = SLABS ? is / n_slab : is;
@@ -2086,7 +2099,7 @@ hipError_t launch_march_bwd(const AccelView &av, const mvp_prims &p, int64_t n_i
   if (R == 0) return hipSuccess;
   RayConst *rc = (RayConst *)scratch;
   RayBound *rbd = (RayBound *)(rc + R);
-  uint32_t *pmax = (uint32_t *)(counters + kCntPayMax);
+  uint32_t *pmax = (uint32_t *)(counters + kCntPayMax), *odd = (uint32_t *)(counters + kCntOdd);
   const bool bf16 = p.payload_dtype == MVP_BF16;
   const bool fade = av.fade_alpha > 0.f;
   const size_t fade_shm = fade ? (size_t)p.M * sizeof(float) : 0;
@@ -2095,14 +2108,14 @@ hipError_t launch_march_bwd(const AccelView &av, const mvp_prims &p, int64_t n_i
   if (n_vox) {
     const unsigned pg = (unsigned)std::min<size_t>((n_vox + 255) / 256, 1024);
     if (bf16)
-      hipLaunchKernelGGL((k_payload_bound<true>), dim3(pg), dim3(256), 0, s, p.payload, n_vox, pmax);
+      hipLaunchKernelGGL((k_payload_bound<true>), dim3(pg), dim3(256), 0, s, p.payload, n_vox, pmax, odd);
     else
-      hipLaunchKernelGGL((k_payload_bound<false>), dim3(pg), dim3(256), 0, s, p.payload, n_vox, pmax);
+      hipLaunchKernelGGL((k_payload_bound<false>), dim3(pg), dim3(256), 0, s, p.payload, n_vox, pmax, odd);
   }
   const unsigned rb = (unsigned)((R + kBwdRaysPerBlock - 1) / kBwdRaysPerBlock);
 #define MVP_RAYS(B, F)                                                                                        \
   hipLaunchKernelGGL((k_bwd_rays<B, F>), dim3(rb), dim3(256), fade_shm, s, av, p.payload, aux,               \
-                     (const float4 *)grad_rgba, bg, (const float4 *)rgba, rc, rbd, pmax, g_bg, R)
+                     (const float4 *)grad_rgba, bg, (const float4 *)rgba, rc, rbd, pmax, odd, g_bg, R)
   if (bf16) {
     if (fade) MVP_RAYS(true, true); else MVP_RAYS(true, false);
   } else {
@@ -2186,10 +2199,12 @@ hipError_t launch_march_bwd(const AccelView &av, const mvp_prims &p, int64_t n_i
     }
   }
   if (t0) (void)hipEventRecord(t0, s);
-  if (n_list) {
+  if (slab_cells) {
     const uint32_t few = (uint32_t)std::min<int64_t>(20 + 4 * n_slab, 100);
-    hipLaunchKernelGGL(k_item_split, dim3((unsigned)((n_items_max + kWave - 1) / kWave)), dim3(kWave), 0, s, av, few, n_list);
-    hipLaunchKernelGGL(bwd_items_fn(bf16, false, fade, runs, BwdShape::kThree), dim3(grid), dim3(kTileThreads),
+    if (n_list)
+      hipLaunchKernelGGL(k_item_split, dim3((unsigned)((n_items_max + kWave - 1) / kWave)), dim3(kWave), 0, s, av, few, n_list);
+    hipLaunchKernelGGL(bwd_items_fn(bf16, false, fade, runs, BwdShape::kThree),
+                       dim3((unsigned)std::min<int64_t>(n_items_max, kSlabGrid)), dim3(kTileThreads),
                        fade_shm + kTileThreads * (sizeof(uint16_t) + 1), s, av, p.rot, p.scale, p.payload, aux,
                        (const float4 *)grad_rgba, rc, rbd, out, (uint32_t)kTileThreads, 0, slab_cells, n_list, counters);
     e = hipGetLastError();
