@@ -340,8 +340,9 @@ __device__ inline void tile_pairs(const AccelView &av, int tile, const PairsOut 
   // 4096 x 8^3 in one 1024^2 view, 64 rays a tile: 116 us, 342 with the line at
   // rays x blocks = len (a wave took 64 rays in turn), 227 with one lane per ray
   // throughout; 16 rays a tile 98, 155 and 201 us, 4 rays 85, 83 and 193 us.
-  constexpr uint64_t kRayCost = 4;
-  const bool sparse = SUBSET && len <= kStage && rays <= kWave && kRayCost * rays * ((len + kWave - 1) / kWave) <= len;
+  constexpr uint32_t kRayCost = 4;
+  const bool sparse = SUBSET && len <= kStage && rays <= kWave &&
+                      kRayCost * (uint32_t)rays * (((uint32_t)len + kWave - 1) / kWave) <= (uint32_t)len;
   int v, px, py;
   size_t ray;
   const bool valid = tile_ray(av, tile, t, &ray, &v, &px, &py);
